@@ -32,7 +32,8 @@ HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E nameplate
 KERNEL_SOURCES = ["paper_2607_05668_amd/csrc/step_kernels.hpp", "paper_2607_05668_amd/csrc/sys_nsf17.hip",
                   "paper_2607_05668_amd/csrc/kernels.hip", "paper_2607_05668_amd/csrc/systems.hpp",
                   "paper_2607_05668_amd/csrc/lattices.hpp", "paper_2607_05668_amd/csrc/impl.hpp",
-                  "paper_2607_05668_amd/csrc/dual.hpp", "paper_2607_05668_amd/csrc/device_common.hpp"]
+                  "paper_2607_05668_amd/csrc/dual.hpp", "paper_2607_05668_amd/csrc/device_common.hpp",
+                  "paper_2607_05668_amd/csrc/collide.hpp"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_nsf256.json")
 
 

@@ -5,6 +5,12 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
+#ifndef LBM_FAST_CONTRACT
+#pragma clang fp contract(on)
+#endif
+
 template <class R, int N>
 struct Dual {
     R v;
@@ -124,4 +130,73 @@ __host__ __device__ inline Dual<R, N> lbm_sqrt(const Dual<R, N> &a)
 #pragma unroll
     for (int j = 0; j < N; ++j) r.d[j] = a.d[j] * s;
     return r;
+}
+
+// Parameter type of kernels that keep populations in float and compute in
+// double (an expression of Wd and double values is plain double arithmetic).
+// Their quotients, roots and logarithms need relative errors far below the
+// 2^-24 of the store they end in, not correct rounding: lbm_div, lbm_sqrt_of
+// and lbm_log1p_of take the parameter type R and use, for Wd, a reciprocal
+// from the float instruction and one Newton step (relative error below
+// 2^-43; 6 instructions against about 16 of the IEEE division), and series of
+// that accuracy.
+struct Wd {
+    double v;
+    Wd() = default;
+    __host__ __device__ constexpr Wd(double x) : v(x) {}
+    __host__ __device__ constexpr operator double() const { return v; }
+};
+
+// 1 / x of a double within the float range
+__host__ __device__ inline double lbm_rcp_wide(double x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double r = (double)__builtin_amdgcn_rcpf((float)x);
+    return fma(r, fma(-x, r, 1.0), r);
+#else
+    return 1.0 / x;
+#endif
+}
+
+template <class R, class S>
+__host__ __device__ inline S lbm_div(const S &a, const S &b)
+{
+    if constexpr (std::is_same<R, Wd>::value)
+        return a * lbm_rcp_wide(b);
+    else
+        return a / b;
+}
+
+template <class R, class S>
+__host__ __device__ inline S lbm_sqrt_of(const S &x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (std::is_same<R, Wd>::value) {
+        // y = x rsqrt(x), one Newton step from the float reciprocal root
+        const double r = (double)__builtin_amdgcn_rsqf((float)x), y = x * r;
+        return fma(fma(-y, y, x), 0.5 * r, y);
+    } else
+#endif
+        return lbm_sqrt(x);
+}
+
+// log(1 + x): for |x| <= 1/4 the series 2 atanh(s), s = x / (2 + x), |s| <=
+// 1/7, seven terms (truncation below 2^-43 of the result)
+template <class R, class S>
+__host__ __device__ inline S lbm_log1p_of(const S &x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (std::is_same<R, Wd>::value) {
+        if (!(fabs(x) <= 0.25)) return log1p(x);
+        const double s = x * lbm_rcp_wide(2.0 + x), s2 = s * s;
+        double t = fma(s2, 1.0 / 15, 1.0 / 13);
+        t = fma(s2, t, 1.0 / 11);
+        t = fma(s2, t, 1.0 / 9);
+        t = fma(s2, t, 1.0 / 7);
+        t = fma(s2, t, 1.0 / 5);
+        t = fma(s2, t, 1.0 / 3);
+        return 2.0 * fma(s * s2, t, s);
+    } else
+#endif
+        return lbm_log1p(x);
 }

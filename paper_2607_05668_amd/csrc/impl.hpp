@@ -64,8 +64,8 @@ struct KParams {
     float scale[LBM_MAXK];            // storage = value * scale (F16 only)
     float inv_scale[LBM_MAXK];
     Phys<R> phys;
-    const R *b;                       // per-cell source field [D][C] or null
-    const R *sext;                    // per-cell explicit source [K][C] added to S_k, or null
+    const void *b;                    // per-cell coefficient field [NB][C], or null, and
+    const void *sext;                 // explicit source [K][C] added to S_k, or null (in the storage's field type)
     MmsParams<R> mms;
 };
 

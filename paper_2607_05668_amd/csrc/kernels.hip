@@ -141,7 +141,7 @@ template <class R>
 KParams<R> lbm_state_impl::kparams(double t_half) const
 {
     KParams<R> p;
-    std::memset(&p, 0, sizeof p);
+    std::memset((void *)&p, 0, sizeof p);
     p.nx = nx;
     p.ny = ny;
     p.nz = nz;
@@ -286,8 +286,8 @@ KParams<R> lbm_state_impl::kparams(double t_half) const
         p.phys.H0[j] = (R)d.H0[j];
         p.phys.P0[j] = (R)d.P0[j];
     }
-    p.b = (const R *)field_b;
-    p.sext = (const R *)field_src;
+    p.b = field_b;
+    p.sext = field_src;
     p.mms.on = (sys == SYS_NSF17) ? mms_on : 0;
     p.mms.amp = (R)mms_amp;
     p.mms.rho0 = (R)mms_rho0;
@@ -325,3 +325,4 @@ const Launchers *lbm_launchers(int sys, int lat, int storage)
 
 template KParams<float> lbm_state_impl::kparams<float>(double) const;
 template KParams<double> lbm_state_impl::kparams<double>(double) const;
+template KParams<Wd> lbm_state_impl::kparams<Wd>(double) const;

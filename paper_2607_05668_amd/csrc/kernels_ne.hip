@@ -21,6 +21,7 @@
 // tile-blocked layout of the step kernels ([tiles][K][Q][kTile], the cells
 // padded to whole tiles), padded to 256 bytes, then moments [K][cells]
 // float.
+#define LBM_FAST_CONTRACT               // one kernel per step only: the compiler may fuse across expressions
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -194,7 +195,7 @@ __global__ __launch_bounds__(kNeTX * kNeTY) void k_step_ne(const _Float16 *__res
     float bl[3] = {0.0f, 0.0f, 0.0f};
     if (p.b) {
 #pragma unroll
-        for (int a = 0; a < D; ++a) bl[a] = p.b[(size_t)a * C + cell];
+        for (int a = 0; a < D; ++a) bl[a] = ((const float *)p.b)[(size_t)a * C + cell];
     }
     Sys::template source<float, float>(p.phys, dQ, bl, Sk);
 #pragma unroll

@@ -27,7 +27,7 @@
 #include <cstring>
 #include <type_traits>
 
-#include "device_common.hpp"
+#include "collide.hpp"
 
 // --------------------------------------------- manufactured forcing ----
 // d_t Q + div Phi(Q) for the 3D NSF manufactured solution (exact fields of
@@ -165,19 +165,12 @@ constexpr int step_block()
     return (sizeof(St) == 8 && Sys::K >= 12) ? kBlock : (Sys::K > 6 ? 512 : kBlock);
 }
 
-// Systems that form their equilibria in float-float from a plain-float
-// flux deviation declare `static constexpr bool ffeq = true` (see k_step).
-template <class Sys, class = void> struct FfeqOf : std::false_type {};
-template <class Sys> struct FfeqOf<Sys, decltype(void(Sys::ffeq))> : std::integral_constant<bool, Sys::ffeq> {};
-
-// collision operators of the step kernel
-enum { COLL_BGK = 0, COLL_TRT = 1, COLL_REG = 2 };
-
 template <class Sys, class Lat, class St, bool REC, bool NT, bool O32, int COLL>
 __global__ __launch_bounds__((step_block<Sys, St>())) void k_step(const St *__restrict__ fin, St *__restrict__ fout,
-                                                            const KParams<typename Store<St>::R> p,
+                                                            const KParams<typename Cell<Sys, Lat, St, COLL>::P> p,
                                                             typename Store<St>::R *__restrict__ qhist)
 {
+    using C = Cell<Sys, Lat, St, COLL>;
     using R = typename Store<St>::R;
     using I = typename Index<O32>::T;
     constexpr int K = Sys::K, Q = Lat::Q, D = Lat::D;
@@ -234,205 +227,13 @@ __global__ __launch_bounds__((step_block<Sys, St>())) void k_step(const St *__re
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            const R v = Store<St>::ld(byte_at(fin + (size_t)zs[i] * slab + (size_t)(k * Q + i) * kTile, src[i]));
-            if constexpr (std::is_same<St, _Float16>::value)
-                f[k][i] = v * (R)p.inv_scale[k];
-            else
-                f[k][i] = v;
-        }
-    // moments (eq. moments) by compensated summation: dQ = hi + lo exactly
-    // up to the rounding of lo (two-sum of each addition).  Binary16 storage
-    // sums plainly: each stored population already carries a rounding of
-    // 2^-12 of its magnitude, where the FP32 sum adds ~Q 2^-24, and the
-    // two-sums would be a fifth of the step's instructions.
-    constexpr bool COMP = Sys::compensated && !std::is_same<St, _Float16>::value;
-    R dQ[K], dQlo[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        R s = f[k][0], c = R(0);
-#pragma unroll
-        for (int i = 1; i < Q; ++i) {
-            const R t = s + f[k][i];
-            if constexpr (COMP) {
-                const R bp = t - s;
-                c += (s - (t - bp)) + (f[k][i] - bp);
-            }
-            s = t;
-        }
-        dQ[k] = s;
-        dQlo[k] = c;
-    }
-    // Single-precision steppers of the precise systems evaluate the flux
-    // deviation at the compensated moments: dPhi(hi) and, from one
-    // forward-mode tangent, its first-order correction J(hi) lo.
-    constexpr bool PRECISE = Sys::precise && !std::is_same<St, _Float16>::value;
-    // per-cell coefficient field (default values when none is attached)
-    using CT = CoefTraits<Sys>;
-    constexpr int NB = CT::NB;
-    R bl[NB > 3 ? NB : 3];
-#pragma unroll
-    for (int a = 0; a < (NB > 3 ? NB : 3); ++a) bl[a] = R(CT::dflt(a));
-    if (p.b) {
-#pragma unroll
-        for (int a = 0; a < NB; ++a) bl[a] = *byte_at(p.b + a * (size_t)p.C, cell * (I)sizeof(R));
-    }
-    R dPhi[K][D], dPhiLo[K][D];
-    static_assert(!(PRECISE && CT::in_flux), "coefficient-dependent fluxes use the plain equilibrium");
-    if constexpr (CT::in_flux) {
-        Sys::template flux_delta_b<R, R>(p.phys, dQ, bl, dPhi);
-    } else if constexpr (PRECISE) {
-        using D1 = Dual<R, 1>;
-        D1 q1[K], P1[K][D];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            q1[k] = D1(dQ[k]);
-            q1[k].d[0] = dQlo[k];
-        }
-        Sys::template flux_delta<D1, R>(p.phys, q1, P1);
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                dPhi[k][a] = P1[k][a].v;
-                dPhiLo[k][a] = P1[k][a].d[0];
-            }
-    } else {
-        Sys::template flux_delta<R, R>(p.phys, dQ, dPhi);
-    }
-    // Float-float equilibria: the precise systems form e = e_hi + e_lo from
-    // the flux deviation and its first-order correction J(hi) lo; the large
-    // tracker states (ffeq) form it from the plain-float flux deviation, the
-    // exact error of lam dPhi included, which keeps the flux evaluation's
-    // register budget.  The velocity-gradient trackers see the momentum's
-    // rounding amplified by |u| / |du| and by 1 / (k dx) (they follow the
-    // gradient of the velocity it carries): with plain-float equilibria their
-    // distance to the FP64 oracle reached 3x the binary32 storage floor at
-    // 128^3, with float-float ones 1.5x.
-    constexpr bool FFEQ = PRECISE || (FfeqOf<Sys>::value && std::is_same<St, float>::value);
-    R Sk[K];
-    Sys::template source<R, R>(p.phys, dQ, bl, Sk);
-    if (p.sext) {
-        // explicit per-cell source (e.g. a manufactured-solution forcing
-        // evaluated at t + dt/2 by the caller)
-#pragma unroll
-        for (int k = 0; k < K; ++k) Sk[k] += *byte_at(p.sext + k * (size_t)p.C, cell * (I)sizeof(R));
-    }
-    if constexpr (Sys::id == SYS_NSF17) {
-#pragma unroll
-        for (int k = 0; k < 5; ++k) Sk[k] += Smms[k];
-    }
-    // BGK relaxation post = omega feq + (1 - omega) f written as
-    // post = e + c1 (e - f) with c1 = omega - 1 exactly representable (the
-    // host places 2 - omega on the 2^-24 grid): e - f is exact when f is
-    // within a factor two of e, so the update rounds once.  In the precise
-    // path e = e_hi + e_lo and post = e_hi + (c1 (e_hi - f) + omega e_lo).
-    // Two-relaxation-time (TRT): with d_i = e_i - f_i and ib the opposite
-    // velocity, relaxing the symmetric and antisymmetric parts at omega+ and
-    // omega- is post_i = f_i + a d_i + b d_ib, a = (omega+ + omega-)/2 (in c1
-    // = a - 1 and c2 = a), b = (omega+ - omega-)/2: the BGK update plus
-    // b d_ib.  Regularized: post_i = e_i + (1 - omega) w_i c_i . Pi1 / cs^2
-    // with Pi1 = sum_i c_i (f_i - e_i), the non-equilibrium part projected
-    // on the first-order Hermite polynomial.
-    // The rest population closes the zeroth moment,
-    // post_0 = f_0 + dt S + sum_{i>0} (f_i - post_i), an identity of the
-    // update (the weights sum to one, the flux enters only odd moments)
-    // evaluated with the stored values of post_i, so each cell's
-    // post-collision moment carries a single storage rounding.
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const R c1 = p.c1[k], c2 = p.c2[k];
-        R s[Q], eh[Q], el[Q];
-        if constexpr (FFEQ) {
-            R Gh[D], Gl[D];
-            FF<R> e[Q];
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                Gh[a] = p.lam * dPhi[k][a];
-                if constexpr (PRECISE)
-                    Gl[a] = fma(p.lam, dPhi[k][a], -Gh[a]) + p.lam * dPhiLo[k][a];
-                else
-                    Gl[a] = fma(p.lam, dPhi[k][a], -Gh[a]);
-            }
-            ExactEqFF<Lat>::feq(dQ[k], dQlo[k], Gh, Gl, e);
-#pragma unroll
-            for (int i = 1; i < Q; ++i) {
-                eh[i] = e[i].hi;
-                el[i] = e[i].lo;
-            }
-        } else {
-            R G[D];
-#pragma unroll
-            for (int a = 0; a < D; ++a) G[a] = p.lam * dPhi[k][a];
-            ExactEq<Lat>::feq(dQ[k], dQlo[k], G, eh);
-        }
-        const R dts = p.dt * Sk[k];
-        ExactEq<Lat>::zeroth(dts, s);
-        R acc = dts;
-        constexpr bool TRT = COLL == COLL_TRT;
-        R bd[Q];                         // TRT: b d_i
-        R P1[D];                         // regularized: sum_i c_i (f_i - e_i)
-        if constexpr (COLL == COLL_REG) {
-#pragma unroll
-            for (int a = 0; a < D; ++a) P1[a] = R(0);
-#pragma unroll
-            for (int i = 1; i < Q; ++i) {
-                R d = f[k][i] - eh[i];
-                if constexpr (FFEQ) d = d - el[i];
-#pragma unroll
-                for (int a = 0; a < D; ++a)
-                    if (lat_c<Lat>(i, a) != 0) P1[a] = lat_c<Lat>(i, a) > 0 ? P1[a] + d : P1[a] - d;
-            }
-        }
-        if constexpr (TRT) {
-            const R tb = p.tb[k];
-#pragma unroll
-            for (int i = 1; i < Q; ++i) {
-                if constexpr (FFEQ)
-                    bd[i] = tb * ((eh[i] - f[k][i]) + el[i]);
-                else
-                    bd[i] = tb * (eh[i] - f[k][i]);
-            }
-        }
-#pragma unroll
-        for (int i = 1; i < Q; ++i) {
-            const R fi = f[k][i];
-            R post;
-            if constexpr (COLL == COLL_REG) {
-                R cp = R(0);
-#pragma unroll
-                for (int a = 0; a < D; ++a)
-                    if (lat_c<Lat>(i, a) != 0) cp = lat_c<Lat>(i, a) > 0 ? cp + P1[a] : cp - P1[a];
-                // (1 - omega) w_i / cs^2 (c_i . Pi1), with w_i / cs^2 = Wn_i / Fden
-                const R rg = (-c1) * (cp * (R(Lat::Wn[i]) / R(Lat::Fden)));
-                if constexpr (FFEQ)
-                    post = eh[i] + ((el[i] + rg) + s[i]);
-                else
-                    post = eh[i] + (rg + s[i]);
-            } else if constexpr (TRT) {
-                if constexpr (FFEQ)
-                    post = eh[i] + (fma(c1, eh[i] - fi, fma(c2, el[i], bd[Lat::opp[i]])) + s[i]);
-                else
-                    post = fma(c1, eh[i] - fi, eh[i] + bd[Lat::opp[i]]) + s[i];
-            } else if constexpr (FFEQ) {
-                post = eh[i] + (fma(c1, eh[i] - fi, c2 * el[i]) + s[i]);
-            } else {
-                post = fma(c1, eh[i] - fi, eh[i]) + s[i];
-            }
-            St *dst = byte_at(fout + (size_t)z * slab + (size_t)(k * Q + i) * kTile, own);
-            if constexpr (std::is_same<St, _Float16>::value) {
-                const _Float16 hv = (_Float16)(post * (R)p.scale[k]);
-                st_pop<NT>(dst, hv);
-                post = (R)hv * (R)p.inv_scale[k];
-            } else {
-                Store<St>::template st<NT>(dst, post);
-            }
-            acc += fi - post;
-        }
-        R rest = f[k][0] + acc;
-        if constexpr (std::is_same<St, _Float16>::value) rest *= (R)p.scale[k];
-        Store<St>::template st<NT>(byte_at(fout + (size_t)z * slab + (size_t)(k * Q) * kTile, own), rest);
-    }
+        for (int i = 0; i < Q; ++i)
+            f[k][i] = Store<St>::ld(byte_at(fin + (size_t)zs[i] * slab + (size_t)(k * Q + i) * kTile, src[i]));
+    const CellFields<R, I> ex = {(const R *)p.b, (const R *)p.sext, (size_t)p.C, cell * (I)sizeof(R)};
+    R dQ[K];
+    C::update(p, f, ex, Smms, dQ, [&](int k, int i, St v) {
+        st_pop<NT>(byte_at(fout + (size_t)z * slab + (size_t)(k * Q + i) * kTile, own), v);
+    });
     if constexpr (REC) {
 #pragma unroll
         for (int k = 0; k < K; ++k) *byte_at(qhist + k * (size_t)p.C, cell * (I)sizeof(R)) = dQ[k];
@@ -672,7 +473,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R *__restrict__ lin, 
     R bl[3] = {R(0), R(0), R(0)};
     if (p.b) {
 #pragma unroll
-        for (int a = 0; a < D; ++a) bl[a] = p.b[(size_t)a * C + cell];
+        for (int a = 0; a < D; ++a) bl[a] = ((const R *)p.b)[(size_t)a * C + cell];
     }
     R mu[K][Q], M0[K], M1[K][D];
 #pragma unroll
@@ -800,11 +601,12 @@ __global__ __launch_bounds__(kBlock) void k_adj_init(const R *__restrict__ lam0,
 template <class Sys, class Lat, class St>
 struct Impl {
     using R = typename Store<St>::R;
+    using P = typename Cell<Sys, Lat, St, COLL_BGK>::P;      // parameter type of the step kernels
     static unsigned grid(long long C) { return (unsigned)((C + kBlock - 1) / kBlock); }
 
     template <bool REC, bool NT, bool O32, int COLL>
     static void launch_step(const lbm_state_impl &h, const void *fin, void *fout, void *qhist, hipStream_t s,
-                            const KParams<R> &p)
+                            const KParams<P> &p)
     {
         constexpr int B = step_block<Sys, St>();
         const long long tpp = ((long long)h.nx * h.ny + B - 1) / B;    // tiles per z-plane
@@ -813,7 +615,7 @@ struct Impl {
     }
     template <bool REC, bool NT, int COLL>
     static void launch_step(const lbm_state_impl &h, const void *fin, void *fout, void *qhist, hipStream_t s,
-                            const KParams<R> &p)
+                            const KParams<P> &p)
     {
         // the 32-bit form needs one z-slab of populations and the history
         // and source planes below 4 GiB
@@ -825,8 +627,8 @@ struct Impl {
     static hipError_t step(const lbm_state_impl &h, const void *fin, void *fout, void *qhist, hipStream_t s)
     {
         const double t_half = h.t0 + (h.nsteps + 0.5) * h.dt;
-        const KParams<R> p = h.kparams<R>(t_half);
-        const bool nt = 2 * (size_t)Sys::K * Lat::Q * sizeof(St) * (size_t)h.C > kLastLevelCacheBytes;
+        const KParams<P> p = h.kparams<P>(t_half);
+        const bool nt = beyond_cache(h);
         const int coll = h.regularized ? COLL_REG : (h.trt_lambda > 0 ? COLL_TRT : COLL_BGK);
         if (qhist && coll != COLL_BGK) return hipErrorInvalidValue;   // the moment history serves the BGK adjoint
         if constexpr (Sys::K <= 6) {
@@ -848,6 +650,10 @@ struct Impl {
             nt ? launch_step<false, true, COLL_BGK>(h, fin, fout, qhist, s, p)
                : launch_step<false, false, COLL_BGK>(h, fin, fout, qhist, s, p);
         return hipGetLastError();
+    }
+    static bool beyond_cache(const lbm_state_impl &h)
+    {
+        return 2 * (size_t)Sys::K * Lat::Q * sizeof(St) * (size_t)h.C > kLastLevelCacheBytes;
     }
     static hipError_t init(const lbm_state_impl &h, const double *Q, void *fout, hipStream_t s)
     {

@@ -16,6 +16,12 @@
 
 #include <type_traits>
 
+// fused multiply-adds only within one source expression: a flux rounds alike
+// in every kernel it is inlined into
+#ifndef LBM_FAST_CONTRACT
+#pragma clang fp contract(on)
+#endif
+
 #define LBM_MAXK 18
 
 // Per-run constants shared by all systems (filled on the host in double and
@@ -50,7 +56,7 @@ struct Phys {
 template <class S, class R>
 __host__ __device__ inline S dquot(R a0, R b0, R q0, const S &da, const S &db, const S &h, const S &dh)
 {
-    return ((a0 * db + b0 * da + da * db) - dh * q0) / h;
+    return lbm_div<R>(S((a0 * db + b0 * da + da * db) - dh * q0), h);
 }
 
 // ------------------------------------------------------------------ SWE --
@@ -58,7 +64,7 @@ __host__ __device__ inline S dquot(R a0, R b0, R q0, const S &da, const S &db, c
 //   Phi_h = hu, Phi_hu = hu (x) u + g h^2/2 I, S_hu = -g h grad z_b.
 struct SysSWE {
     static constexpr int K = 3, D = 2, id = 1;
-    static constexpr bool precise = true;    // float-float equilibrium in single precision
+    static constexpr bool precise = true;    // flux in double (float storage), float-float equilibrium (double)
     static constexpr bool compensated = true;   // two-sum moments dQ = hi + lo
     static constexpr bool tracker(int) { return false; }
 
@@ -102,7 +108,7 @@ struct SysSWE {
 // d(u^2 / 2) = du (u0 + du / 2).
 struct SysBurgers {
     static constexpr int K = 1, D = 2, id = 4;
-    static constexpr bool precise = true;    // float-float equilibrium in single precision
+    static constexpr bool precise = true;    // flux in double (float storage), float-float equilibrium (double)
     static constexpr bool compensated = true;   // two-sum moments dQ = hi + lo
     static constexpr bool tracker(int) { return false; }
 
@@ -137,7 +143,7 @@ struct SysBurgers {
 // and d(H m_c / rho) with H = E + p.
 struct SysEuler {
     static constexpr int K = 4, D = 2, id = 5;
-    static constexpr bool precise = true;    // float-float equilibrium in single precision
+    static constexpr bool precise = true;    // flux in double (float storage), float-float equilibrium (double)
     static constexpr bool compensated = true;   // two-sum moments dQ = hi + lo
     static constexpr bool tracker(int) { return false; }
 
@@ -185,7 +191,7 @@ struct SysEuler {
 // source.  Linear, so dPhi is the flux of dQ.
 struct SysMaxwell {
     static constexpr int K = 3, D = 2, id = 6;
-    static constexpr bool precise = true;    // float-float equilibrium in single precision
+    static constexpr bool precise = true;    // flux in double (float storage), float-float equilibrium (double)
     static constexpr bool compensated = true;   // two-sum moments dQ = hi + lo
     static constexpr bool tracker(int) { return false; }
 
@@ -222,7 +228,7 @@ struct SysMaxwell {
 // S_phi = r (phi - phi^3), S_G = -G / tau_grad; gamma in nu, r in react.
 struct SysAllenCahn {
     static constexpr int K = 3, D = 2, id = 7;
-    static constexpr bool precise = true;    // float-float equilibrium in single precision
+    static constexpr bool precise = true;    // flux in double (float storage), float-float equilibrium (double)
     static constexpr bool compensated = true;   // two-sum moments dQ = hi + lo
     static constexpr bool tracker(int k) { return k > 0; }
 
@@ -263,7 +269,7 @@ struct SysAllenCahn {
 // (sqrt + sqrt0), dp = (d sqrt - dE) / 3, S (x) S / H through dquot.
 struct SysRelHydro {
     static constexpr int K = 3, D = 2, id = 8;
-    static constexpr bool precise = true;    // float-float equilibrium in single precision
+    static constexpr bool precise = true;    // flux in double (float storage), float-float equilibrium (double)
     static constexpr bool compensated = true;   // two-sum moments dQ = hi + lo
     static constexpr bool tracker(int) { return false; }
 
@@ -273,9 +279,9 @@ struct SysRelHydro {
         const R E0 = p.Q0[0], Sx0 = p.Q0[1], Sy0 = p.Q0[2];
         const S dE = dQ[0], dSx = dQ[1], dSy = dQ[2];
         const S E = dE + E0, Sx = dSx + Sx0, Sy = dSy + Sy0;
-        const S sq = lbm_sqrt(E * E * R(4) - (Sx * Sx + Sy * Sy) * R(3));
+        const S sq = lbm_sqrt_of<R>(E * E * R(4) - (Sx * Sx + Sy * Sy) * R(3));
         const S num = dE * (dE + R(2) * E0) * R(4) - (dSx * (dSx + R(2) * Sx0) + dSy * (dSy + R(2) * Sy0)) * R(3);
-        const S dp = (num / (sq + p.sq_ref) - dE) * R(1.0 / 3.0);
+        const S dp = (lbm_div<R>(num, S(sq + p.sq_ref)) - dE) * R(1.0 / 3.0);
         const S dH = dE + dp;
         const S H = dH + p.H_ref;
         const S xy = dquot(Sx0, Sy0, p.mm0_h0[1], dSx, dSy, H, dH);
@@ -311,7 +317,7 @@ struct SysRelHydro {
 // the tracker rows are wave-uniform and formed in the kernel.
 struct SysNSE {
     static constexpr int K = 7, D = 2, id = 9;
-    static constexpr bool precise = true;    // float-float equilibrium in single precision
+    static constexpr bool precise = true;    // flux in double (float storage), float-float equilibrium (double)
     static constexpr bool compensated = true;   // two-sum moments dQ = hi + lo
     static constexpr bool tracker(int k) { return k >= 3; }
 
@@ -332,7 +338,7 @@ struct SysNSE {
                 const S conv = dquot(m0[a], m0[c], p.mm0_h0[q], dm[a], dm[c], r, dr);
                 const R X0 = p.Q0[3 + 2 * a + c] + p.Q0[3 + 2 * c + a];
                 const S dX = dQ[3 + 2 * a + c] + dQ[3 + 2 * c + a];
-                const S visc = (dX - dr * (X0 / r0)) / r;
+                const S visc = lbm_div<R>(S(dX - dr * (X0 / r0)), r);
                 dPhi[1 + a][c] = (a == c) ? conv + dr * p.cs2_phys - visc * p.mu : conv - visc * p.mu;
             }
 #pragma unroll
@@ -340,7 +346,7 @@ struct SysNSE {
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
                     const R G0 = p.Q0[3 + 2 * a + b];
-                    const S tr = dquot(G0, m0[c], G0 * m0[c] / r0, dQ[3 + 2 * a + b], dm[c], r, dr);
+                    const S tr = dquot(G0, m0[c], R(G0 * m0[c] / r0), dQ[3 + 2 * a + b], dm[c], r, dr);
                     dPhi[3 + 2 * a + b][c] = (b == c) ? tr - dm[a] * p.inv_tau_grad : tr;
                 }
         }
@@ -377,7 +383,7 @@ struct SysNSE {
 // trackers are small, as value minus reference value.
 struct SysCNSF2D {
     static constexpr int K = 12, D = 2, id = 10;
-    static constexpr bool precise = false;   // plain exact-moment equilibrium (VALU budget)
+    static constexpr bool precise = false;   // flux in the storage's arithmetic (register budget)
     static constexpr bool compensated = true;   // two-sum moments dQ = hi + lo
     static constexpr bool tracker(int k) { return k >= 4; }
 
@@ -489,7 +495,7 @@ struct SysCNSF2D {
 // (small where the trackers are small) as value minus reference value.
 struct SysMHD {
     static constexpr int K = 18, D = 2, id = 11;
-    static constexpr bool precise = false;   // plain exact-moment equilibrium (VALU budget)
+    static constexpr bool precise = false;   // flux in the storage's arithmetic (register budget)
     static constexpr bool compensated = true;   // two-sum moments dQ = hi + lo
     static constexpr bool tracker(int k) { return k >= 6; }
 
@@ -616,7 +622,7 @@ struct SysMHD {
 // the flux of dQ.
 struct SysAdvDiff {
     static constexpr int K = 3, D = 2, id = 0;
-    static constexpr bool precise = true;    // float-float equilibrium in single precision
+    static constexpr bool precise = true;    // flux in double (float storage), float-float equilibrium (double)
     static constexpr bool compensated = true;   // two-sum moments dQ = hi + lo
     static constexpr bool tracker(int k) { return k > 0; }
 
@@ -660,7 +666,7 @@ struct SysAdvDiff {
 // F - F^{-T} = (J F - cof F) / J, all formed from the small entries of H.
 struct SysNeoHooke {
     static constexpr int K = 6, D = 2, id = 2;
-    static constexpr bool precise = true;    // float-float equilibrium in single precision
+    static constexpr bool precise = true;    // flux in double (float storage), float-float equilibrium (double)
     static constexpr bool compensated = true;   // two-sum moments dQ = hi + lo
     static constexpr bool tracker(int) { return false; }
 
@@ -668,8 +674,8 @@ struct SysNeoHooke {
     __host__ __device__ static void stress(const Phys<R> &p, const S H[4], S P[4])
     {
         const S dJ = H[0] + H[3] + H[0] * H[3] - H[1] * H[2];
-        const S invJ = R(1) / (dJ + R(1));
-        const S lnJ = lbm_log1p(dJ);
+        const S invJ = lbm_div<R>(S(R(1)), S(dJ + R(1)));
+        const S lnJ = lbm_log1p_of<R>(dJ);
         // cof F = [[1 + H11, -H10], [-H01, 1 + H00]]
         const S c00 = H[3] + R(1), c01 = -H[2], c10 = -H[1], c11 = H[0] + R(1);
         // J F - cof F
@@ -762,8 +768,7 @@ struct SysNeoHooke {
 // every product ab - a0 b0 written as da b + a0 db.
 struct SysNSF17 {
     static constexpr int K = 17, D = 3, id = 3;
-    static constexpr bool precise = false;   // no dual-number flux correction (register budget)
-    static constexpr bool ffeq = true;       // float-float equilibria from the plain-float flux
+    static constexpr bool precise = false;   // flux in the storage's arithmetic (register budget)
     static constexpr bool compensated = true;   // two-sum moments dQ = hi + lo
     static constexpr bool tracker(int k) { return k >= 5; }
 
@@ -859,8 +864,7 @@ struct SysNSF17 {
 // dissipative terms is the terms themselves.
 struct SysHCNSF {
     static constexpr int K = 14, D = 3, id = 12;
-    static constexpr bool precise = false;   // no dual-number flux correction (register budget)
-    static constexpr bool ffeq = true;       // float-float equilibria from the plain-float flux
+    static constexpr bool precise = false;   // flux in the storage's arithmetic (register budget)
     static constexpr bool compensated = true;
     static constexpr bool tracker(int k) { return k >= 5; }
     // coefficient field: 4 values per cell, read by the flux as well
