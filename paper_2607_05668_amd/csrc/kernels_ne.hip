@@ -447,6 +447,7 @@ struct ImplNE {
             o32 ? launch<false, true>(h, fin, fout, p, s) : launch<false, false>(h, fin, fout, p, s);
         return hipGetLastError();
     }
+    static int steps_per_launch(const lbm_state_impl &, int) { return 1; }
     static hipError_t init(const lbm_state_impl &h, const double *Q, void *fout, hipStream_t s)
     {
         hipLaunchKernelGGL((k_init_ne<Sys, Lat>), dim3(grid(h.C)), dim3(kBlock), 0, s, Q, (_Float16 *)fout,
@@ -485,7 +486,7 @@ struct ImplNE {
     }
     static const Launchers *get()
     {
-        static const Launchers L = {Sys::K, Lat::Q, Lat::D, 2, step, init, init_absmax, moments,
+        static const Launchers L = {Sys::K, Lat::Q, Lat::D, 2, steps_per_launch, step, nullptr, init, init_absmax, moments,
                                     reduce, nullptr, nullptr, nullptr};
         return &L;
     }

@@ -756,6 +756,22 @@ static int check_finite(lbm_state *h)
     return LBM_OK;
 }
 
+// Enqueue `left` steps on s, as few launches as the kernels allow, alternating
+// the population buffers from cur on; counts left down.
+static hipError_t enqueue_steps(lbm_state *h, int &left, char *qhist, size_t stride, int &cur, hipStream_t s)
+{
+    while (left > 0) {
+        const int m = h->L->steps_per_launch(*h, left);
+        void *const in = h->pop[cur], *const out = h->pop[cur ^ 1];
+        const hipError_t e = m > 1 ? h->L->multi(*h, m, in, out, qhist, s) : h->L->step(*h, in, out, qhist, s);
+        if (e != hipSuccess) return e;
+        cur ^= 1;
+        left -= m;
+        if (qhist) qhist += (size_t)m * stride;
+    }
+    return hipSuccess;
+}
+
 static int run_steps(lbm_state *h, int n, void *qhist)
 {
     int rc = check_ready(h);
@@ -768,19 +784,23 @@ static int run_steps(lbm_state *h, int n, void *qhist)
             char *q0 = qhist ? (char *)qhist + (size_t)j * stride : nullptr;
             const GraphKey key = {0, len, h->cur, h->epoch, {h->pop[0], h->pop[1], q0, nullptr}};
             const int cur0 = h->cur;
+            int cur = cur0;
+            for (int left = len; left > 0; cur ^= 1) left -= h->L->steps_per_launch(*h, left);
             rc = replay(h, key, [&](hipStream_t s) {
-                int c = cur0;
-                for (int i = 0; i < len; ++i) {
-                    const hipError_t e = h->L->step(*h, h->pop[c], h->pop[c ^ 1], q0 ? q0 + (size_t)i * stride : nullptr, s);
-                    if (e != hipSuccess) return e;
-                    c ^= 1;
-                }
-                return hipSuccess;
+                int c = cur0, left = len;
+                return enqueue_steps(h, left, q0, stride, c, s);
             });
             if (rc) return rc;
-            h->cur ^= len & 1;
+            h->cur = cur;
             h->nsteps += len;
         }
+    }
+    if (j < n && h->check_every == 0 && !(h->sys == SYS_NSF17 && h->mms_on)) {
+        int left = n - j;
+        const hipError_t e = enqueue_steps(h, left, qhist ? (char *)qhist + (size_t)j * stride : nullptr, stride, h->cur,
+                                           h->stream);
+        h->nsteps += n - j - left;
+        return e == hipSuccess ? LBM_OK : hipfail(h, e, "step");
     }
     for (; j < n; ++j) {
         void *q = qhist ? (char *)qhist + (size_t)j * stride : nullptr;

@@ -1,0 +1,279 @@
+// Several collide-and-stream steps of a 2D grid in one launch.
+//
+// A step by itself moves every population through HBM once each way, and the
+// 2D steps spend their time on that.  Here a wavefront marches up a strip of
+// 64 columns, row by row: stage 1 pulls a row of populations from the buffer
+// and collides it, stage 2 collides the row below from the stage-1 rows
+// around it, and so on; only the last stage's rows are stored, T steps on.
+// The intermediate rows live on the chip: a population moving up waits two
+// rows and one moving along the row waits one, in this wavefront's own part
+// of LDS, where a neighbouring column is a neighbouring word; one moving down
+// is used at once, pulled from the neighbouring lane by a wave-wide DPP shift.
+// Wavefronts share nothing and meet no barrier.
+//
+// Price: T - 1 lanes at each end of the strip and T - 1 rows at each end of
+// the march are computed but not stored (stage t needs T - t of them), so a
+// wavefront stores 64 - 2 (T - 1) columns of every row of its segment.  Those
+// are no whole cache lines: the stores are plain ones, so that L2 joins the
+// parts of two strips (non-temporal stores: 19% slower at 2048^2).
+//
+// Bound: with one or two wavefronts a SIMD the vector units issue for about
+// two thirds of the time (shallow water 2048^2, four stages: 40 of 61 us per
+// step); the rest is the partial cache lines' stores (misaligned stores alone
+// cost 18 us at three stages, misaligned loads nothing).
+#pragma once
+
+#include <algorithm>
+
+#include "collide.hpp"
+
+// The value of lane l - 1 (C = +1) or l + 1 (C = -1); zero past the ends.
+template <int C>
+__device__ __forceinline__ float lane_pull(float v)
+{
+    if constexpr (C == 0) return v;
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), C > 0 ? 0x138 : 0x130, 0xf, 0xf, true));
+}
+template <int C>
+__device__ __forceinline__ double lane_pull(double v)
+{
+    if constexpr (C == 0) return v;
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), C > 0 ? 0x138 : 0x130, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), C > 0 ? 0x138 : 0x130, 0xf, 0xf, true));
+}
+template <class Lat, class F>
+__device__ __forceinline__ F lane_pull(F v, int i)      // i a constant after unrolling
+{
+    return Lat::cx[i] > 0 ? lane_pull<1>(v) : (Lat::cx[i] < 0 ? lane_pull<-1>(v) : v);
+}
+
+// A buffer store whose lanes with off >= 2^31 are dropped by the range check,
+// so the marching loop has no branch around its stores.
+template <class T>
+__device__ __forceinline__ void st_masked(__amdgpu_buffer_rsrc_t r, unsigned off, int base, T v)
+{
+        constexpr int aux = 0;
+    if constexpr (sizeof(T) == 8) {
+        typedef int v2 __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2, v), r, off, base, aux);
+    } else if constexpr (sizeof(T) == 4) {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), r, off, base, aux);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(short, v), r, off, base, aux);
+    }
+}
+
+// A load through a buffer descriptor: uniform base, one 32-bit offset per lane.
+template <class T>
+__device__ __forceinline__ T ld_buf(__amdgpu_buffer_rsrc_t r, unsigned off, int base)
+{
+    if constexpr (sizeof(T) == 8)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, base, 0));
+    else if constexpr (sizeof(T) == 4)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, base, 0));
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(r, off, base, 0));
+}
+
+// Keeps the compiler from moving LDS accesses of one lane across those of
+// others in the wavefront (which executes them in order).
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Populations of a field that wait between two stages, and the LDS that a
+// wavefront of T stages keeps.
+template <class Lat> constexpr int march_slots() { return Lat::Q == 9 ? 9 : 5; }
+template <class Sys, class Lat, class St>
+constexpr int march_lds(int T) { return ((T - 1) * march_slots<Lat>() * Sys::K * 64 + 2) * (int)sizeof(St); }
+
+// Steps per launch of a large grid: four, where that leaves seven wavefronts
+// a CU their LDS, else three or two.  Shallow water 2048^2, D2Q9, float, us
+// per step: 152 one step per launch, 120, 86, 61 two, three and four; five
+// (five wavefronts a CU) 66.
+constexpr int kLdsPerCu = 160 * 1024;
+template <class Sys, class Lat, class St>
+constexpr int march_most()
+{
+    int T = 4;
+    while (T > 2 && 7 * march_lds<Sys, Lat, St>(T) > kLdsPerCu) --T;
+    return T;
+}
+
+// Whether two stages leave eight wavefronts a CU (two a SIMD) their LDS, and
+// a state fits the registers of two wavefronts a SIMD.
+template <class Sys, class Lat, class St>
+constexpr bool marches()
+{
+    return Lat::D == 2 && Sys::K <= 7 && 8 * march_lds<Sys, Lat, St>(2) <= kLdsPerCu;
+}
+
+// Rows of a wavefront's segment.  A wavefront of T stages collides
+// T rows + T (T - 1) rows, so few long segments cost least, but one wavefront
+// a SIMD is the least that fills the chip; a second one hides the latencies of
+// the first and costs 1.75 times its time in place of twice (up to 30
+// populations; 1.5 times with more).  Counts just above one or two wavefronts a
+// SIMD leave a SIMD with one more than the others: shallow water 512^2, four
+// stages, rows 3 / 4 / 6 (1539, 1152, 774 wavefronts): 7.4 / 8.0 / 7.1 us per
+// step.
+constexpr int kSimds = 1024;
+template <class Sys, class Lat, class St>
+inline int march_rows(int T, int nx, int ny)
+{
+    const int strips = (nx + 64 - 2 * (T - 1) - 1) / (64 - 2 * (T - 1));
+    const int two = std::min(2 * kSimds, kSimds / 4 * (kLdsPerCu / march_lds<Sys, Lat, St>(T)));
+    auto rows_for = [&](int waves) {
+        const int segments = std::max(1, waves / strips);
+        return (ny + segments - 1) / segments;
+    };
+    const int r1 = rows_for(kSimds), r2 = rows_for(two);
+    const double c1 = r1 + T - 1, c2 = (Sys::K * Lat::Q <= 30 ? 1.75 : 1.5) * (r2 + T - 1);
+    return c1 <= c2 ? r1 : r2;
+}
+
+template <class Sys, class Lat, class St, int T, bool EXT, bool REC, int COLL>
+__global__ __launch_bounds__(64) void k_march(const St *__restrict__ fin, St *__restrict__ fout,
+                                              const KParams<typename Cell<Sys, Lat, St, COLL>::P> p,
+                                              typename Store<St>::R *__restrict__ qhist, int rows, int strips)
+{
+    using C = Cell<Sys, Lat, St, COLL>;
+    using F = typename Store<St>::R;
+    constexpr int K = Sys::K, Q = Lat::Q, KQ = K * Q;
+    constexpr int HALO = T - 1, WOUT = 64 - 2 * HALO;
+    const int lane = (int)threadIdx.x;                                    // one wavefront per workgroup
+    const unsigned g = (unsigned)xcd_tile(blockIdx.x, gridDim.x);
+    const int strip = (int)(g % (unsigned)strips);
+    const int y0 = (int)(g / (unsigned)strips) * rows, y1 = y0 + rows < p.ny ? y0 + rows : p.ny;
+    const int xo = strip * WOUT + lane - HALO;                            // unwrapped column
+    const bool mine = lane >= HALO && lane < 64 - HALO && xo < p.nx;      // column stored by this lane
+    int xw = xo % p.nx;
+    xw = xw < 0 ? xw + p.nx : xw;
+    const int xs[3] = {wrapi(xw - 1, p.nx), xw, wrapi(xw + 1, p.nx)};
+
+    // Offsets of a row: its first cell y nx lies b cells into tile a; the
+    // tile's part is uniform, a lane's part stays below 2^31.
+    struct Row {
+        size_t base;            // elements to tile a
+        unsigned b;             // y nx - 64 a
+    };
+    auto row_of = [&](int y) {
+        const size_t c = (size_t)y * (size_t)p.nx;
+        return Row{c / kTile * (size_t)(KQ * kTile), (unsigned)(c % kTile)};
+    };
+    auto lane_off = [&](const Row &r, int x) { return tile_offset<K, Q>(r.b + (unsigned)x) * (unsigned)sizeof(St); };
+    auto rsrc = [](const St *base) {
+        return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, 0x7fffffff, 0x00027000);
+    };
+
+    // the row that stage 1 loads next
+    int yn = (y0 - HALO) % p.ny;
+    yn = yn < 0 ? yn + p.ny : yn;
+    const int last = y1 - y0 + 2 * HALO - 1;
+    // Two rows of populations: one at work, the next on its way from memory.
+    // The march alternates between them, so that no register copy waits for
+    // the loads; past the last row it loads that row again.
+    St in[2][K][Q];
+    auto load = [&](St (&to)[K][Q], bool more) {
+        const Row rw[3] = {row_of(wrapi(yn - 1, p.ny)), row_of(yn), row_of(wrapi(yn + 1, p.ny))};
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const Row &r = rw[1 - Lat::cy[i]];
+            const auto rs = rsrc(fin + r.base);
+            const unsigned off = lane_off(r, xs[1 - Lat::cx[i]]);
+#pragma unroll
+            for (int k = 0; k < K; ++k) to[k][i] = ld_buf<St>(rs, off, (k * Q + i) * kTile * (int)sizeof(St));
+        }
+        yn = more ? wrapi(yn + 1, p.ny) : yn;
+    };
+    // Stage s's populations on their way: slots of 64 words, two rows of those
+    // moving up (by the row's parity), then those moving along the row.  Lane
+    // 0's left and lane 63's right neighbour are other slots' words: lanes at
+    // the ends are not stored.
+    constexpr int NU = Lat::Q == 9 ? 3 : 1, NW = march_slots<Lat>();
+    static_assert(NW == 2 * NU + 3, "two rows of those moving up, one of those along it");
+    __shared__ St carry[march_lds<Sys, Lat, St>(T) / sizeof(St)];
+    St *const wait = &carry[1 + lane];
+    // slot of population i of field k after stage s, parity of its row
+    constexpr auto slot = [](int s, int k, int i, int par) {
+        int n = Lat::cy[i] > 0 ? par * NU : 2 * NU;
+        for (int j = 0; j < i; ++j) n += Lat::cy[j] == Lat::cy[i];
+        return ((s * NW + n) * K + k) * 64;
+    };
+    // one row of the march with the first NS stages at work; the last stage of
+    // a full march stores row y0 + j - 2 HALO
+    auto row = [&](auto ns, auto parity, int j) {
+        constexpr int NS = decltype(ns)::value, par = decltype(parity)::value;
+        F f[K][Q];
+        load(in[par ^ 1], j + 1 < last);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int i = 0; i < Q; ++i) f[k][i] = (F)in[par][k][i];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            const int yu = y0 - HALO + j - s;                             // this stage's row, unwrapped
+            int y = yu;
+            if constexpr (EXT || REC) {
+                y = yu % p.ny;
+                y = y < 0 ? y + p.ny : y;
+            }
+            const CellFields<F, size_t, EXT> ex = {(const F *)p.b, (const F *)p.sext, (size_t)p.C,
+                                                   ((size_t)y * (size_t)p.nx + (unsigned)xw) * sizeof(F)};
+            F dQ[K];
+            St post[K][Q];
+            if (s == HALO) {                                              // rows y0 to y1 only: none wraps
+                const Row out = row_of(yu);
+                const auto rs = rsrc(fout + out.base);
+                const unsigned off = mine ? lane_off(out, xw) : 0x80000000u;
+                C::update(p, f, ex, nullptr, dQ, [&](int k, int i, St v) {
+                    st_masked(rs, off, (k * Q + i) * kTile * (int)sizeof(St), v);
+                });
+            } else {
+                C::update(p, f, ex, nullptr, dQ, [&](int k, int i, St v) { post[k][i] = v; });
+                // read what the rows below left before this row takes its place
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+#pragma unroll
+                    for (int i = 0; i < Q; ++i)
+                        f[k][i] = Lat::cy[i] < 0 ? lane_pull<Lat>((F)post[k][i], i)
+                                                 : (F)wait[slot(s, k, i, par) - Lat::cx[i]];
+                wave_fence();
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+#pragma unroll
+                    for (int i = 0; i < Q; ++i)
+                        if (Lat::cy[i] >= 0) wait[slot(s, k, i, par)] = post[k][i];
+                wave_fence();
+            }
+            if constexpr (REC) {
+                if (mine && yu >= y0 && yu < y1) {
+#pragma unroll
+                    for (int k = 0; k < K; ++k) *byte_at(qhist + (s * (size_t)K + k) * (size_t)p.C, ex.off) = dQ[k];
+                }
+            }
+        }
+    };
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, 1> odd{};
+    load(in[0], true);
+    // fill: stage s + 1 joins two rows after stage s
+    auto fill = [&](auto self, auto ns) {
+        constexpr int NS = decltype(ns)::value;
+        if constexpr (NS < T) {
+            row(ns, even, 2 * NS - 2);
+            row(ns, odd, 2 * NS - 1);
+            self(self, std::integral_constant<int, NS + 1>());
+        }
+    };
+    fill(fill, std::integral_constant<int, 1>());
+    constexpr std::integral_constant<int, T> all{};
+    for (int j = 2 * HALO;; j += 2) {
+        row(all, even, j);
+        if (j == last) break;
+        row(all, odd, j + 1);
+        if (j + 1 == last) break;
+    }
+}

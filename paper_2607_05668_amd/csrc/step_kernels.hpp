@@ -24,10 +24,11 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <algorithm>
 #include <cstring>
 #include <type_traits>
 
-#include "collide.hpp"
+#include "march.hpp"
 
 // --------------------------------------------- manufactured forcing ----
 // d_t Q + div Phi(Q) for the 3D NSF manufactured solution (exact fields of
@@ -651,6 +652,64 @@ struct Impl {
                : launch_step<false, false, COLL_BGK>(h, fin, fout, qhist, s, p);
         return hipGetLastError();
     }
+    // ---- several steps per launch (k_march) ----
+    static constexpr bool kMarch = marches<Sys, Lat, St>();
+    static constexpr int kMost = kMarch ? march_most<Sys, Lat, St>() : 1;
+    // Steps of the next launch when `want` are left (1: k_step).  A grid of at
+    // most 700 strip rows (wavefronts of one row each) takes two steps a
+    // launch: the launch costs as much as the arithmetic of a row, and SIMDs
+    // are free for the halo (shallow water 64^2: 2.93 -> 2.60 us per step, 150
+    // x 101: 3.11 -> 2.86).  Up to 2000 strip rows the chip has no room for
+    // the halo (256^2: one step 3.77, two 4.10, three 4.02 us); beyond, fewer
+    // passes over memory pay (384^2: 6.0 -> 5.3, 512^2: 9.3 -> 7.0).
+    static int steps_per_launch(const lbm_state_impl &h, int want)
+    {
+        if (!kMarch || want < 2 || h.regularized) return 1;
+        // a row's lane offsets stay below 2^31 bytes
+        if ((long long)(h.nx + kTile) * Sys::K * Lat::Q * (long long)sizeof(St) >= 1ll << 31) return 1;
+        const long long strip_rows = (long long)((h.nx + 61) / 62) * h.ny;
+        if (strip_rows <= 700) return 2;
+        if (strip_rows < 2000) return 1;
+        return want >= kMost && !(kMost == 3 && want == 4) ? kMost : 2;
+    }
+    template <int T, bool EXT, bool REC, int COLL>
+    static void launch_march(const lbm_state_impl &h, const void *fin, void *fout, void *qhist, hipStream_t s)
+    {
+        const KParams<P> p = h.kparams<P>(h.t0);
+        const int strips = (h.nx + 64 - 2 * (T - 1) - 1) / (64 - 2 * (T - 1));
+        const int rows = march_rows<Sys, Lat, St>(T, h.nx, h.ny);
+        hipLaunchKernelGGL((k_march<Sys, Lat, St, T, EXT, REC, COLL>), dim3((unsigned)(strips * ((h.ny + rows - 1) / rows))),
+                           dim3(64), 0, s, (const St *)fin, (St *)fout, p, (R *)qhist, rows, strips);
+    }
+    template <int T>
+    static hipError_t launch_march(const lbm_state_impl &h, const void *fin, void *fout, void *qhist, hipStream_t s)
+    {
+        const bool ext = h.field_b || h.field_src;
+        if (qhist) {
+            if constexpr (Sys::K <= 6) {
+                if (h.trt_lambda > 0) return hipErrorInvalidValue;       // the moment history serves the BGK adjoint
+                launch_march<T, true, true, COLL_BGK>(h, fin, fout, qhist, s);
+            } else {
+                return hipErrorInvalidValue;
+            }
+        } else if (h.trt_lambda > 0) {
+            launch_march<T, true, false, COLL_TRT>(h, fin, fout, nullptr, s);
+        } else if (ext) {
+            launch_march<T, true, false, COLL_BGK>(h, fin, fout, nullptr, s);
+        } else {
+            launch_march<T, false, false, COLL_BGK>(h, fin, fout, nullptr, s);
+        }
+        return hipGetLastError();
+    }
+    static hipError_t multi(const lbm_state_impl &h, int steps, const void *fin, void *fout, void *qhist, hipStream_t s)
+    {
+        if constexpr (kMarch) {
+            if (steps == 2) return launch_march<2>(h, fin, fout, qhist, s);
+            if constexpr (kMost > 2)
+                if (steps == kMost) return launch_march<kMost>(h, fin, fout, qhist, s);
+        }
+        return hipErrorInvalidValue;
+    }
     static bool beyond_cache(const lbm_state_impl &h)
     {
         return 2 * (size_t)Sys::K * Lat::Q * sizeof(St) * (size_t)h.C > kLastLevelCacheBytes;
@@ -718,11 +777,11 @@ struct Impl {
     {
         // the adjoint is provided for the 2D systems (K <= 6)
         if constexpr (Sys::K <= 6) {
-            static const Launchers L = {Sys::K, Lat::Q, Lat::D, sizeof(St), step, init, init_absmax, moments,
+            static const Launchers L = {Sys::K, Lat::Q, Lat::D, sizeof(St), steps_per_launch, step, multi, init, init_absmax, moments,
                                         reduce, adj_seed, adj_step, adj_init};
             return &L;
         } else {
-            static const Launchers L = {Sys::K, Lat::Q, Lat::D, sizeof(St), step, init, init_absmax, moments,
+            static const Launchers L = {Sys::K, Lat::Q, Lat::D, sizeof(St), steps_per_launch, step, multi, init, init_absmax, moments,
                                         reduce, nullptr, nullptr, nullptr};
             return &L;
         }
