@@ -101,6 +101,28 @@ __device__ inline size_t pop_at(int k, int i, long long c, long long P)
     return (size_t)z * K * Q * (size_t)Pp + (size_t)tile_offset<K, Q>(c - z * P) + (size_t)(k * Q + i) * kTile;
 }
 
+// Element offsets of the places x - c_i of a cell's populations (k = 0): where
+// they are pulled from and where the initialisation writes them; population k
+// lies k Q kTile further.  I: the type of cell indices, 32-bit wherever the
+// grid has fewer than 2^32 cells (their divisions by the extents are most of
+// the arithmetic of a kernel that only sums populations).
+template <int K, class Lat, class I>
+__device__ inline void pulled_places(I cell, int nx, int ny, int nz, size_t *at)
+{
+    int x, y, z;
+    cell_coords<I>(cell, nx, ny, x, y, z);
+    const I P = (I)nx * (I)ny;
+    const size_t slab = (size_t)K * Lat::Q * ((P + (I)(kTile - 1)) / (I)kTile) * kTile;
+#pragma unroll
+    for (int i = 0; i < Lat::Q; ++i) {
+        const I c = (I)wrapi(y - Lat::cy[i], ny) * (I)nx + (I)wrapi(x - Lat::cx[i], nx);
+        const int zs = Lat::D == 3 ? wrapi(z - Lat::cz[i], nz) : 0;
+        at[i] = (size_t)zs * slab + (size_t)(c / (I)kTile) * (size_t)(K * Lat::Q * kTile) + (size_t)(c % (I)kTile)
+                + (size_t)(i * kTile);
+    }
+}
+inline bool fits_i32(long long C) { return C < (1ll << 32) - (1ll << 26); }   // also with a grid stride added
+
 // A thread reaches population (k, i) of a cell through the wave-uniform
 // base of its z-slab shifted by (k Q + i) kTile elements (kept in scalar
 // registers) plus a per-lane byte offset inside the slab.  When a slab is

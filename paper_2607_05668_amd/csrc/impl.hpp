@@ -28,6 +28,7 @@ constexpr int kBlock = LBM_BLOCK;    // threads per workgroup (wave64 multiples)
 // non-temporal stores: MI355X's Infinity Cache holds 256 MiB.
 constexpr size_t kLastLevelCacheBytes = (size_t)256 << 20;
 constexpr int kRedBlocks = 1024;     // workgroups of the first reduction pass
+constexpr int kInitBlocks = 16384;   // most workgroups of the initialisation (partial maxima in the reduction scratch)
 // Population layout: each z-slab's nx*ny cells are cut into tiles of kTile
 // consecutive cells (x fastest, rows continue into the next tile), and a
 // tile keeps all K*Q populations of its cells together,
@@ -80,7 +81,9 @@ struct Launchers {
     int (*steps_per_launch)(const lbm_state_impl &, int want);
     hipError_t (*step)(const lbm_state_impl &, const void *fin, void *fout, void *qhist, hipStream_t);
     hipError_t (*multi)(const lbm_state_impl &, int steps, const void *fin, void *fout, void *qhist, hipStream_t);
-    hipError_t (*init)(const lbm_state_impl &, const double *Q, void *fout, hipStream_t);
+    // speed: reduction scratch or null; gets the largest wave speed in the
+    // final slot of a LBM_RED_MAXSPEED reduction
+    hipError_t (*init)(const lbm_state_impl &, const double *Q, void *fout, double *speed, hipStream_t);
     hipError_t (*init_absmax)(const lbm_state_impl &, const double *Q, double *partial, hipStream_t);
     hipError_t (*moments)(const lbm_state_impl &, const void *fin, void *out, int absolute, int out_dtype,
                           hipStream_t);

@@ -448,16 +448,19 @@ struct ImplNE {
         return hipGetLastError();
     }
     static int steps_per_launch(const lbm_state_impl &, int) { return 1; }
-    static hipError_t init(const lbm_state_impl &h, const double *Q, void *fout, hipStream_t s)
+    static hipError_t init(const lbm_state_impl &h, const double *Q, void *fout, double *speed, hipStream_t s)
     {
         hipLaunchKernelGGL((k_init_ne<Sys, Lat>), dim3(grid(h.C)), dim3(kBlock), 0, s, Q, (_Float16 *)fout,
                            (float *)mp(h, fout), h.kparams<double>(h.t0), h.kparams<float>(h.t0));
-        return hipGetLastError();
+        const hipError_t e = hipGetLastError();
+        return e != hipSuccess || !speed ? e : reduce(h, fout, 3, nullptr, speed, s);
     }
     static hipError_t init_absmax(const lbm_state_impl &h, const double *Q, double *part, hipStream_t s)
     {
         hipLaunchKernelGGL((k_init_absmax_ne<Sys, Lat>), dim3(kRedBlocks), dim3(kBlock), 0, s, Q, part,
                            h.kparams<double>(h.t0), h.kparams<float>(h.t0));
+        hipLaunchKernelGGL(k_reduce2_ne, dim3(1), dim3(kBlock), 0, s, part, part + (size_t)2 * LBM_MAXK * kRedBlocks,
+                           Sys::K, kRedBlocks, 1);
         return hipGetLastError();
     }
     static hipError_t moments(const lbm_state_impl &h, const void *fin, void *out, int absolute, int out_dtype,

@@ -694,6 +694,16 @@ int lbm_set_field(lbm_state *h, const char *name, const void *dev_ptr)
     return fail(h, LBM_EINVAL, std::string("unknown field '") + name + "' for this system");
 }
 
+// The first n final slots of a reduction with scratch ws, on the host (waits
+// for the stream).
+static int fetch_slots(lbm_state *h, const double *ws, int n, double *out)
+{
+    hipError_t e = hipMemcpyAsync(out, ws + (size_t)2 * LBM_MAXK * kRedBlocks, n * sizeof(double), hipMemcpyDeviceToHost,
+                                  h->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    return e == hipSuccess ? LBM_OK : hipfail(h, e, "reduce copy");
+}
+
 int lbm_reduce(lbm_state *h, int what, const double *ref_dev, double *host_out);
 
 int lbm_init_moments(lbm_state *h, const double *Q_dev)
@@ -708,13 +718,11 @@ int lbm_init_moments(lbm_state *h, const double *Q_dev)
         // maps near 2^11 (binary16 holds up to 65504)
         e = h->L->init_absmax(*h, Q_dev, (double *)h->aux, h->stream);
         if (e != hipSuccess) return hipfail(h, e, "init_absmax");
-        std::vector<double> part((size_t)h->K * kRedBlocks);
-        e = hipMemcpyAsync(part.data(), h->aux, part.size() * sizeof(double), hipMemcpyDeviceToHost, h->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-        if (e != hipSuccess) return hipfail(h, e, "init_absmax copy");
+        double largest[LBM_MAXK];
+        rc = fetch_slots(h, (double *)h->aux, h->K, largest);
+        if (rc) return rc;
         for (int k = 0; k < h->K; ++k) {
-            double m = 0.0;
-            for (int b = 0; b < kRedBlocks; ++b) m = std::fmax(m, part[(size_t)k * kRedBlocks + b]);
+            const double m = largest[k];
             int ex = 0;
             if (m > 0.0 && std::isfinite(m)) ex = (int)std::floor(std::log2(2048.0 / m));
             h->scale_exp[k] = ex < -24 ? -24 : (ex > 24 ? 24 : ex);
@@ -723,16 +731,17 @@ int lbm_init_moments(lbm_state *h, const double *Q_dev)
     h->cur = 0;
     h->nsteps = 0;
     h->epoch += 1;                      // the F16 scales may have changed
-    e = h->L->init(*h, Q_dev, h->pop[0], h->stream);
+    e = h->L->init(*h, Q_dev, h->pop[0], h->check_subchar ? (double *)h->aux : nullptr, h->stream);
     if (e != hipSuccess) return hipfail(h, e, "init");
     if (h->check_subchar) {
-        double sp[2];
-        rc = lbm_reduce(h, LBM_RED_MAXSPEED, nullptr, sp);
+        double speed;
+        rc = fetch_slots(h, (double *)h->aux, 1, &speed);
         if (rc) return rc;
-        if (!(sp[1] <= 1.0)) {
+        speed *= h->dt / h->dx;
+        if (!(speed / std::sqrt(h->cs2) <= 1.0)) {
             char buf[160];
             std::snprintf(buf, sizeof buf, "sub-characteristic bound violated: (dt/dx) max|eig A_n| = %.6g > cs = %.6g",
-                          sp[0], std::sqrt(h->cs2));
+                          speed, std::sqrt(h->cs2));
             return fail(h, LBM_ESUBCHAR, buf);
         }
     }
@@ -848,10 +857,8 @@ static int reduce_with(lbm_state *h, int what, const double *ref_dev, double *ho
     if (e != hipSuccess) return hipfail(h, e, "reduce");
     const int nslot = (what == LBM_RED_MAXSPEED || what == LBM_RED_NONFINITE) ? 1 : (what == LBM_RED_SUMS ? h->K : 2 * h->K);
     double r[2 * LBM_MAXK];
-    e = hipMemcpyAsync(r, ws + (size_t)2 * LBM_MAXK * kRedBlocks, nslot * sizeof(double), hipMemcpyDeviceToHost,
-                       h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-    if (e != hipSuccess) return hipfail(h, e, "reduce copy");
+    rc = fetch_slots(h, ws, nslot, r);
+    if (rc) return rc;
     switch (what) {
     case LBM_RED_SUMS:
         for (int k = 0; k < h->K; ++k) host_out[k] = r[k];

@@ -262,33 +262,52 @@ __device__ inline void init_flux_delta(const Phys<double> &ph, const double *dQ,
     }
 }
 
-template <class Sys, class Lat, class St>
+// With part non-null each workgroup also leaves the largest wave speed of its
+// cells there (the sub-characteristic check), from the moments of the values
+// as stored: the thread that writes a cell's populations holds all of them,
+// where a separate reduction reads the whole buffer back (shallow water
+// 2048^2: 145 us after the 110 us of this kernel).
+template <class Sys, class Lat, class St, class I>
 __global__ __launch_bounds__(kBlock) void k_init(const double *__restrict__ Qin, St *__restrict__ fout,
                                                  const KParams<double> p,
-                                                 const typename Store<St>::R *__restrict__ coef)
+                                                 const typename Store<St>::R *__restrict__ coef,
+                                                 double *__restrict__ part)
 {
     constexpr int K = Sys::K, Q = Lat::Q, D = Lat::D;
-    const long long cell = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (cell >= p.C) return;
-    int x, y, z;
-    cell_coords(cell, p.nx, p.ny, x, y, z);
-    long long dst[Q];
-    neighbours<Lat>(x, y, z, p.nx, p.ny, p.nz, -1, dst);
+    __shared__ double sh[kBlock / 64];
     const size_t C = (size_t)p.C;
-    double dQ[K], dPhi[K][D];
+    double fastest = 0.0;
+    for (I cell = (I)blockIdx.x * kBlock + threadIdx.x; cell < (I)p.C; cell += (I)gridDim.x * kBlock) {
+        size_t dst[Q];
+        pulled_places<K, Lat, I>(cell, p.nx, p.ny, p.nz, dst);
+        double dQ[K], dPhi[K][D], q[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) dQ[k] = Qin[(size_t)k * C + cell] - p.phys.Q0[k];
-    init_flux_delta<Sys, D>(p.phys, dQ, coef, C, cell, dPhi);
+        for (int k = 0; k < K; ++k) dQ[k] = Qin[(size_t)k * C + cell] - p.phys.Q0[k];
+        init_flux_delta<Sys, D>(p.phys, dQ, coef, C, cell, dPhi);
 #pragma unroll
-    for (int k = 0; k < K; ++k)
+        for (int k = 0; k < K; ++k) {
+            double s = 0.0;
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            double cd = 0.0;
+            for (int i = 0; i < Q; ++i) {
+                double cd = 0.0;
 #pragma unroll
-            for (int a = 0; a < D; ++a) cd += lat_c<Lat>(i, a) * dPhi[k][a];
-            const double feq = Lat::w[i] * (dQ[k] + p.lam_cs2 * cd);
-            Store<St>::st_init(fout + pop_at<K, Q>(k, i, dst[i], (long long)p.nx * p.ny), feq * (double)p.scale[k]);
+                for (int a = 0; a < D; ++a) cd += lat_c<Lat>(i, a) * dPhi[k][a];
+                const double feq = Lat::w[i] * (dQ[k] + p.lam_cs2 * cd);
+                const St v = (St)(feq * (double)p.scale[k]);
+                fout[dst[i] + (size_t)(k * Q * kTile)] = v;
+                s += (double)v;
+            }
+            q[k] = s * (double)p.inv_scale[k] + p.phys.Q0[k];
         }
+        if (part) {
+            const double v = Sys::template max_speed<double>(p.phys, q);
+            fastest = v > fastest ? v : fastest;
+        }
+    }
+    if (part) {
+        const double r = block_reduce_max(fastest, sh);
+        if (threadIdx.x == 0) part[blockIdx.x] = r;
+    }
 }
 
 // per-block maxima of |f*eq_{k,i}| per field (chooses the F16 scales)
@@ -326,24 +345,21 @@ __global__ __launch_bounds__(kBlock) void k_init_absmax(const double *__restrict
 }
 
 // ----------------------------------------------------------- moments ----
-template <class Sys, class Lat, class St, class Out>
+template <class Sys, class Lat, class St, class Out, class I>
 __global__ __launch_bounds__(kBlock) void k_moments(const St *__restrict__ fin, Out *__restrict__ out,
                                                     const KParams<double> p, int absolute)
 {
     constexpr int K = Sys::K, Q = Lat::Q;
-    const long long cell = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (cell >= p.C) return;
-    int x, y, z;
-    cell_coords(cell, p.nx, p.ny, x, y, z);
-    long long src[Q];
-    neighbours<Lat>(x, y, z, p.nx, p.ny, p.nz, -1, src);
+    const I cell = (I)xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    if (cell >= (I)p.C) return;
+    size_t src[Q];
+    pulled_places<K, Lat, I>(cell, p.nx, p.ny, p.nz, src);
     const size_t C = (size_t)p.C;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         double s = 0.0;
 #pragma unroll
-        for (int i = 0; i < Q; ++i)
-            s += (double)Store<St>::ld(fin + pop_at<K, Q>(k, i, src[i], (long long)p.nx * p.ny));
+        for (int i = 0; i < Q; ++i) s += (double)Store<St>::ld(fin + src[i] + (size_t)(k * Q * kTile));
         s *= (double)p.inv_scale[k];
         out[(size_t)k * C + cell] = (Out)(absolute ? s + p.phys.Q0[k] : s);
     }
@@ -353,7 +369,7 @@ __global__ __launch_bounds__(kBlock) void k_moments(const St *__restrict__ fin, 
 // First pass: each workgroup grid-strides over cells and writes its partial
 // results [slot][block]; second pass: one workgroup combines the partials
 // in a fixed order (deterministic).
-template <class Sys, class Lat, class St>
+template <class Sys, class Lat, class St, class I>
 __global__ __launch_bounds__(kBlock) void k_reduce1(const St *__restrict__ fin, const double *__restrict__ ref,
                                                     double *__restrict__ part, const KParams<double> p, int what)
 {
@@ -362,14 +378,19 @@ __global__ __launch_bounds__(kBlock) void k_reduce1(const St *__restrict__ fin, 
     const size_t C = (size_t)p.C;
     const unsigned nb = gridDim.x;
     if (what == 4) {   // non-finite populations (the padding of a slab's last tile is not read)
+        // a tile's populations are K Q words of each of its cells: a wavefront
+        // takes a tile, a lane one cell
         double cnt = 0.0;
-        const size_t P = (size_t)p.nx * p.ny, slab = (size_t)K * Q * (size_t)padded_plane((long long)P);
-        const size_t n = slab * p.nz;
-        for (size_t j = (size_t)blockIdx.x * kBlock + threadIdx.x; j < n; j += (size_t)nb * kBlock) {
-            const size_t r = j % slab;
-            if ((r / ((size_t)K * Q * kTile)) * kTile + r % kTile >= P) continue;
-            const double v = (double)Store<St>::ld(fin + j);
-            cnt += isfinite(v) ? 0.0 : 1.0;
+        const I P = (I)p.nx * (I)p.ny, tiles = (P + (I)(kTile - 1)) / (I)kTile;
+        const I waves = (I)nb * (kBlock / 64);
+        for (I t = (I)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); t < tiles * (I)p.nz; t += waves) {
+            const unsigned lane = threadIdx.x & 63u;
+            if (t % tiles * (I)kTile + lane >= P) continue;
+            const St *cell = fin + (size_t)t * (size_t)(K * Q * kTile) + lane;
+            int bad = 0;
+#pragma unroll
+            for (int j = 0; j < K * Q; ++j) bad += isfinite((typename Store<St>::R)cell[(size_t)j * kTile]) ? 0 : 1;
+            cnt += bad;
         }
         const double r = block_reduce_sum(cnt, sh);
         if (threadIdx.x == 0) part[blockIdx.x] = r;
@@ -378,18 +399,15 @@ __global__ __launch_bounds__(kBlock) void k_reduce1(const St *__restrict__ fin, 
     double a0[K], a1[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) a0[k] = a1[k] = 0.0;
-    for (long long cell = (long long)blockIdx.x * kBlock + threadIdx.x; cell < p.C; cell += (long long)nb * kBlock) {
-        int x, y, z;
-        cell_coords(cell, p.nx, p.ny, x, y, z);
-        long long src[Q];
-        neighbours<Lat>(x, y, z, p.nx, p.ny, p.nz, -1, src);
+    for (I cell = (I)blockIdx.x * kBlock + threadIdx.x; cell < (I)p.C; cell += (I)nb * kBlock) {
+        size_t src[Q];
+        pulled_places<K, Lat, I>(cell, p.nx, p.ny, p.nz, src);
         double q[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             double s = 0.0;
 #pragma unroll
-            for (int i = 0; i < Q; ++i)
-                s += (double)Store<St>::ld(fin + pop_at<K, Q>(k, i, src[i], (long long)p.nx * p.ny));
+            for (int i = 0; i < Q; ++i) s += (double)Store<St>::ld(fin + src[i] + (size_t)(k * Q * kTile));
             q[k] = s * (double)p.inv_scale[k] + p.phys.Q0[k];
         }
         if (what == 0) {
@@ -423,12 +441,14 @@ __global__ __launch_bounds__(kBlock) void k_reduce1(const St *__restrict__ fin, 
     }
 }
 
+// one workgroup per slot
 static __global__ __launch_bounds__(kBlock) void k_reduce2(const double *__restrict__ part,
                                                            double *__restrict__ out, int nslot, int nb, int is_max)
 {
     __shared__ double sh[kBlock / 64];
-    for (int j = 0; j < nslot; ++j) {
-        double v = is_max ? 0.0 : 0.0;
+    for (int j = blockIdx.x; j < nslot; j += gridDim.x) {
+        double v = 0.0;
+#pragma unroll 8
         for (int b = threadIdx.x; b < nb; b += kBlock) {
             const double w = part[(size_t)j * nb + b];
             v = is_max ? (w > v ? w : v) : v + w;
@@ -436,6 +456,14 @@ static __global__ __launch_bounds__(kBlock) void k_reduce2(const double *__restr
         const double r = is_max ? block_reduce_max(v, sh) : block_reduce_sum(v, sh);
         if (threadIdx.x == 0) out[j] = r;
     }
+}
+
+// Workgroups of the first pass: enough wavefronts for eight a SIMD, no more
+// than the cells need, and nslot partial results of each within the scratch.
+inline unsigned reduce_blocks(long long C, int nslot)
+{
+    const long long most = std::min<long long>(2 * kRedBlocks, (long long)2 * LBM_MAXK * kRedBlocks / nslot);
+    return (unsigned)std::max<long long>(1, std::min(most, (C + kBlock - 1) / kBlock));
 }
 
 // ------------------------------------------------------------ adjoint ----
@@ -714,11 +742,17 @@ struct Impl {
     {
         return 2 * (size_t)Sys::K * Lat::Q * sizeof(St) * (size_t)h.C > kLastLevelCacheBytes;
     }
-    static hipError_t init(const lbm_state_impl &h, const double *Q, void *fout, hipStream_t s)
+    static hipError_t init(const lbm_state_impl &h, const double *Q, void *fout, double *speed, hipStream_t s)
     {
         const KParams<double> p = h.kparams<double>(h.t0);
-        hipLaunchKernelGGL((k_init<Sys, Lat, St>), dim3(grid(h.C)), dim3(kBlock), 0, s, Q, (St *)fout, p,
-                           (const R *)h.field_b);
+        const unsigned nb = std::min(grid(h.C), (unsigned)kInitBlocks);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, s, Q, (St *)fout, p, (const R *)h.field_b, speed);
+        };
+        fits_i32(h.C) ? go(k_init<Sys, Lat, St, unsigned>) : go(k_init<Sys, Lat, St, unsigned long long>);
+        if (speed)
+            hipLaunchKernelGGL(k_reduce2, dim3(1), dim3(kBlock), 0, s, speed,
+                               speed + (size_t)2 * LBM_MAXK * kRedBlocks, 1, (int)nb, 1);
         return hipGetLastError();
     }
     static hipError_t init_absmax(const lbm_state_impl &h, const double *Q, double *part, hipStream_t s)
@@ -726,30 +760,40 @@ struct Impl {
         const KParams<double> p = h.kparams<double>(h.t0);
         hipLaunchKernelGGL((k_init_absmax<Sys, Lat, R>), dim3(kRedBlocks), dim3(kBlock), 0, s, Q, part, p,
                            (const R *)h.field_b);
+        hipLaunchKernelGGL(k_reduce2, dim3(Sys::K), dim3(kBlock), 0, s, part, part + (size_t)2 * LBM_MAXK * kRedBlocks,
+                           Sys::K, kRedBlocks, 1);
         return hipGetLastError();
     }
     static hipError_t moments(const lbm_state_impl &h, const void *fin, void *out, int absolute, int out_dtype,
                               hipStream_t s)
     {
         const KParams<double> p = h.kparams<double>(h.t0);
+        auto go = [&](auto kern, auto *to) {
+            hipLaunchKernelGGL(kern, dim3(grid(h.C)), dim3(kBlock), 0, s, (const St *)fin, to, p, absolute);
+        };
+        using U = unsigned;
+        using L = unsigned long long;
         if (out_dtype == 0)
-            hipLaunchKernelGGL((k_moments<Sys, Lat, St, double>), dim3(grid(h.C)), dim3(kBlock), 0, s,
-                               (const St *)fin, (double *)out, p, absolute);
+            fits_i32(h.C) ? go(k_moments<Sys, Lat, St, double, U>, (double *)out)
+                          : go(k_moments<Sys, Lat, St, double, L>, (double *)out);
         else
-            hipLaunchKernelGGL((k_moments<Sys, Lat, St, float>), dim3(grid(h.C)), dim3(kBlock), 0, s,
-                               (const St *)fin, (float *)out, p, absolute);
+            fits_i32(h.C) ? go(k_moments<Sys, Lat, St, float, U>, (float *)out)
+                          : go(k_moments<Sys, Lat, St, float, L>, (float *)out);
         return hipGetLastError();
     }
     static hipError_t reduce(const lbm_state_impl &h, const void *fin, int what, const double *ref, double *aux,
                              hipStream_t s)
     {
         const KParams<double> p = h.kparams<double>(h.t0);
-        hipLaunchKernelGGL((k_reduce1<Sys, Lat, St>), dim3(kRedBlocks), dim3(kBlock), 0, s, (const St *)fin, ref,
-                           aux, p, what);
         const int nslot = (what == 3 || what == 4) ? 1 : (what == 0 ? Sys::K : 2 * Sys::K);
         const int is_max = (what == 2 || what == 3) ? 1 : 0;
-        hipLaunchKernelGGL(k_reduce2, dim3(1), dim3(kBlock), 0, s, aux, aux + (size_t)2 * LBM_MAXK * kRedBlocks,
-                           nslot, kRedBlocks, is_max);
+        const unsigned nb = reduce_blocks(h.C, nslot);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, s, (const St *)fin, ref, aux, p, what);
+        };
+        fits_i32(h.C) ? go(k_reduce1<Sys, Lat, St, unsigned>) : go(k_reduce1<Sys, Lat, St, unsigned long long>);
+        hipLaunchKernelGGL(k_reduce2, dim3(nslot), dim3(kBlock), 0, s, aux, aux + (size_t)2 * LBM_MAXK * kRedBlocks,
+                           nslot, (int)nb, is_max);
         return hipGetLastError();
     }
     static hipError_t adj_seed(const lbm_state_impl &h, const void *dLdQ, void *lam, hipStream_t s)
