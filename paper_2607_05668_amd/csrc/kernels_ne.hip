@@ -21,13 +21,12 @@
 // tile-blocked layout of the step kernels ([tiles][K][Q][kTile], the cells
 // padded to whole tiles), padded to 256 bytes, then moments [K][cells]
 // float.
-#define LBM_FAST_CONTRACT               // one kernel per step only: the compiler may fuse across expressions
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstring>
 
-#include "device_common.hpp"
+#include "march.hpp"
 
 inline size_t ne_pop_bytes(long long C, int K, int Q)
 {
@@ -72,6 +71,47 @@ __device__ inline void ne_load(const _Float16 *__restrict__ g, const float *__re
 #pragma unroll
         for (int k = 0; k < K; ++k)
             f[k][i] = (float)g[ne_at<K, Q>(k, i, src[i])] * p.inv_scale[k] + ei[k];
+    }
+}
+
+// Collision of one cell from its pulled populations: emit(k, i, deviation in
+// the stored form, the cell's own equilibrium e_i); dQ: the moments.
+template <class Sys, class Lat, class Emit>
+__device__ __forceinline__ void ne_collide(const KParams<float> &p, const float (&f)[Sys::K][Lat::Q], const float *bl,
+                                           float *dQ, Emit &&emit)
+{
+    constexpr int K = Sys::K, Q = Lat::Q, D = Lat::D;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        float s = f[k][0];
+#pragma unroll
+        for (int i = 1; i < Q; ++i) s += f[k][i];
+        dQ[k] = s;
+    }
+    float dPhi[K][D], Sk[K];
+    Sys::template flux_delta<float, float>(p.phys, dQ, dPhi);
+    Sys::template source<float, float>(p.phys, dQ, bl, Sk);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        float G[D], e[Q], s[Q];
+#pragma unroll
+        for (int a = 0; a < D; ++a) G[a] = p.lam * dPhi[k][a];
+        ExactEq<Lat>::feq(dQ[k], 0.0f, G, e);
+        const float e0 = ExactEq<Lat>::rest(dQ[k]);
+        const float dts = p.dt * Sk[k];
+        ExactEq<Lat>::zeroth(dts, s);
+        float acc = dts;
+#pragma unroll
+        for (int i = 1; i < Q; ++i) {
+            const float d = e[i] - f[k][i];
+            const _Float16 hv = (_Float16)(fmaf(p.c1[k], d, s[i]) * p.scale[k]);
+            emit(k, i, hv, e[i]);
+            // f - e is exactly -d and hv / scale is exact: the closure's
+            // (f - e) - hv / scale is -(d + hv / scale), rounded once
+            acc -= fmaf((float)hv, p.inv_scale[k], d);
+        }
+        const float g0 = (f[k][0] - e0) + acc;
+        emit(k, 0, (_Float16)(g0 * p.scale[k]), e0);
     }
 }
 
@@ -181,45 +221,172 @@ __global__ __launch_bounds__(kNeTX * kNeTY) void k_step_ne(const _Float16 *__res
             f[k][i] = fmaf((float)gr[k][i / 2][i % 2], p.inv_scale[k], ei);      // the scaling is exact
         }
     }
-    float dQ[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        float s = f[k][0];
-#pragma unroll
-        for (int i = 1; i < Q; ++i) s += f[k][i];
-        dQ[k] = s;
-    }
-    float dPhi[K][D];
-    Sys::template flux_delta<float, float>(p.phys, dQ, dPhi);
-    float Sk[K];
-    float bl[3] = {0.0f, 0.0f, 0.0f};
+    float dQ[K], bl[3] = {0.0f, 0.0f, 0.0f};
     if (p.b) {
 #pragma unroll
         for (int a = 0; a < D; ++a) bl[a] = ((const float *)p.b)[(size_t)a * C + cell];
     }
-    Sys::template source<float, float>(p.phys, dQ, bl, Sk);
+    ne_collide<Sys, Lat>(p, f, bl, dQ, [&](int k, int i, _Float16 v, float) {
+        st_pop<NT>(byte_at(gout + (size_t)(k * Q + i) * kTile, own), v);
+    });
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        float G[D], e[Q], s[Q];
+    for (int k = 0; k < K; ++k) st_pop<NT>(Mout + (size_t)k * C + cell, dQ[k]);
+}
+
+// Several steps per launch, as k_march (march.hpp) does for the other
+// storages, with one stage more: stage 0 takes a row's deviations and moments
+// as stored, both from the cell itself, and forms the populations that the
+// cell sent, g_i + e_i(M) with one flux evaluation per cell; from there on a
+// sent population is the same sum of the stage's own values, rounded through
+// binary16 like a stored one.  So T steps take T flux evaluations and one more
+// per cell, where T launches of k_step_ne take 2.55 T, and the deviations and
+// moments cross memory once.  Bit for bit the steps of k_step_ne.
+template <class Sys, class Lat> constexpr int ne_march_lds(int T)
+{
+    return (T * march_slots<Lat>() * Sys::K * 64 + 2) * (int)sizeof(float);
+}
+// steps per launch that leave five wavefronts a CU their LDS (neo-Hookean
+// D2Q9 two, shallow water D2Q9 and the smaller D2Q5 states four)
+template <class Sys, class Lat> constexpr int ne_march_most()
+{
+    int T = 4;
+    while (T > 1 && 5 * ne_march_lds<Sys, Lat>(T) > kLdsPerCu) --T;
+    return T;
+}
+
+template <class Sys, class Lat, int T, bool EXT>
+__global__ __launch_bounds__(64) void k_march_ne(const _Float16 *__restrict__ gin, const float *__restrict__ Min,
+                                                 _Float16 *__restrict__ gout, float *__restrict__ Mout,
+                                                 const KParams<float> p, int rows, int strips)
+{
+    constexpr int K = Sys::K, Q = Lat::Q, D = Lat::D, HALO = T;
+    const int lane = (int)threadIdx.x;
+    const unsigned g = (unsigned)xcd_tile(blockIdx.x, gridDim.x);
+    const int strip = (int)(g % (unsigned)strips);
+    const int y0 = (int)(g / (unsigned)strips) * rows, y1 = y0 + rows < p.ny ? y0 + rows : p.ny;
+    const int xo = strip * (64 - 2 * HALO) + lane - HALO;                 // unwrapped column
+    const bool mine = lane >= HALO && lane < 64 - HALO && xo < p.nx;      // column stored by this lane
+    int xw = xo % p.nx;
+    xw = xw < 0 ? xw + p.nx : xw;
+    const size_t C = (size_t)p.C;
+    auto rsrc = [](const void *base) {
+        return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, 0x7fffffff, 0x00027000);
+    };
+    int yn = (y0 - HALO) % p.ny;                                          // the row that stage 0 loads next
+    yn = yn < 0 ? yn + p.ny : yn;
+    const int last = y1 - y0 + 2 * HALO - 1;
+    // two rows of stored values: one at work, the next on its way (see k_march)
+    _Float16 gi[2][K][Q];
+    float mi[2][K];
+    auto load = [&](_Float16 (&gt)[K][Q], float (&mt)[K], bool more) {
+        const size_t c = (size_t)yn * (size_t)p.nx;
+        const unsigned off = tile_offset<K, Q>((unsigned)(c % kTile) + (unsigned)xw) * 2u;
+        const auto rg = rsrc(gin + c / kTile * (size_t)(K * Q * kTile));
 #pragma unroll
-        for (int a = 0; a < D; ++a) G[a] = p.lam * dPhi[k][a];
-        ExactEq<Lat>::feq(dQ[k], 0.0f, G, e);
-        const float e0 = ExactEq<Lat>::rest(dQ[k]);
-        const float dts = p.dt * Sk[k];
-        ExactEq<Lat>::zeroth(dts, s);
-        float acc = dts;
+        for (int k = 0; k < K; ++k) mt[k] = ld_buf<float>(rsrc(Min + k * C + c), (unsigned)xw * 4u, 0);
 #pragma unroll
-        for (int i = 1; i < Q; ++i) {
-            const float d = e[i] - f[k][i];
-            const _Float16 hv = (_Float16)(fmaf(p.c1[k], d, s[i]) * p.scale[k]);
-            st_pop<NT>(byte_at(gout + (size_t)(k * Q + i) * kTile, own), hv);
-            // f - e is exactly -d and hv / scale is exact: the closure's
-            // (f - e) - hv / scale is -(d + hv / scale), rounded once
-            acc -= fmaf((float)hv, p.inv_scale[k], d);
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int i = 0; i < Q; ++i) gt[k][i] = ld_buf<_Float16>(rg, off, (k * Q + i) * kTile * 2);
+        yn = more ? wrapi(yn + 1, p.ny) : yn;
+    };
+    // populations on their way between stages, as in k_march
+    constexpr int NU = Lat::Q == 9 ? 3 : 1, NW = march_slots<Lat>();
+    __shared__ float carry[ne_march_lds<Sys, Lat>(T) / sizeof(float)];
+    float *const wait = &carry[1 + lane];
+    constexpr auto slot = [](int s, int k, int i, int par) {
+        int n = Lat::cy[i] > 0 ? par * NU : 2 * NU;
+        for (int j = 0; j < i; ++j) n += Lat::cy[j] == Lat::cy[i];
+        return ((s * NW + n) * K + k) * 64;
+    };
+    // one row of the march with stages 0 to NS at work
+    auto row = [&](auto ns, auto parity, int j) {
+        constexpr int NS = decltype(ns)::value, par = decltype(parity)::value;
+        load(gi[par ^ 1], mi[par ^ 1], j + 1 < last);
+        __builtin_amdgcn_sched_barrier(0);
+        float post[K][Q], f[K][Q];
+        {
+            float P[K][D];
+            Sys::template flux_delta<float, float>(p.phys, mi[par], P);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                float G[D], e[Q];
+#pragma unroll
+                for (int a = 0; a < D; ++a) G[a] = p.lam * P[k][a];
+                ExactEq<Lat>::feq(mi[par][k], 0.0f, G, e);
+                e[0] = ExactEq<Lat>::rest(mi[par][k]);
+#pragma unroll
+                for (int i = 0; i < Q; ++i) post[k][i] = fmaf((float)gi[par][k][i], p.inv_scale[k], e[i]);
+            }
         }
-        const float g0 = (f[k][0] - e0) + acc;
-        st_pop<NT>(byte_at(gout + (size_t)(k * Q) * kTile, own), (_Float16)(g0 * p.scale[k]));
-        st_pop<NT>(Mout + (size_t)k * C + cell, dQ[k]);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            // the populations sent by stage s arrive a row below; what the rows
+            // below left is read before this row takes its place
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int i = 0; i < Q; ++i)
+                    f[k][i] = Lat::cy[i] < 0 ? lane_pull<Lat>(post[k][i], i) : wait[slot(s, k, i, par) - Lat::cx[i]];
+            wave_fence();
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int i = 0; i < Q; ++i)
+                    if (Lat::cy[i] >= 0) wait[slot(s, k, i, par)] = post[k][i];
+            wave_fence();
+            const int yu = y0 - HALO + j - s - 1;                         // this stage's row, unwrapped
+            float dQ[K], bl[3] = {0.0f, 0.0f, 0.0f};
+            if (EXT) {
+                int y = yu % p.ny;
+                y = y < 0 ? y + p.ny : y;
+#pragma unroll
+                for (int a = 0; a < D; ++a)
+                    bl[a] = ((const float *)p.b)[a * C + (size_t)y * (size_t)p.nx + (unsigned)xw];
+            }
+            if (s == T - 1) {                                             // rows y0 to y1 only: none wraps
+                const size_t c = (size_t)yu * (size_t)p.nx;
+                const unsigned off = mine ? tile_offset<K, Q>((unsigned)(c % kTile) + (unsigned)xw) * 2u : 0x80000000u;
+                const auto rg = rsrc(gout + c / kTile * (size_t)(K * Q * kTile));
+                ne_collide<Sys, Lat>(p, f, bl, dQ, [&](int k, int i, _Float16 v, float) {
+                    st_masked(rg, off, (k * Q + i) * kTile * 2, v);
+                });
+#pragma unroll
+                for (int k = 0; k < K; ++k) st_masked(rsrc(Mout + k * C + c), mine ? (unsigned)xw * 4u : 0x80000000u, 0, dQ[k]);
+            } else {
+                ne_collide<Sys, Lat>(p, f, bl, dQ, [&](int k, int i, _Float16 v, float e) {
+                    post[k][i] = fmaf((float)v, p.inv_scale[k], e);
+                });
+            }
+        }
+        if constexpr (NS < T) {                                           // the next stage has not begun
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int i = 0; i < Q; ++i)
+                    if (Lat::cy[i] >= 0) wait[slot(NS, k, i, par)] = post[k][i];
+            wave_fence();
+        }
+    };
+    constexpr std::integral_constant<int, 0> even{};
+    constexpr std::integral_constant<int, 1> odd{};
+    load(gi[0], mi[0], true);
+    // fill: a stage joins two rows after the one before it
+    auto fill = [&](auto self, auto ns) {
+        constexpr int NS = decltype(ns)::value;
+        if constexpr (NS < T) {
+            row(ns, even, 2 * NS);
+            row(ns, odd, 2 * NS + 1);
+            self(self, std::integral_constant<int, NS + 1>());
+        }
+    };
+    fill(fill, even);
+    constexpr std::integral_constant<int, T> all{};
+    for (int j = 2 * HALO;; j += 2) {
+        row(all, even, j);
+        if (j == last) break;
+        row(all, odd, j + 1);
+        if (j + 1 == last) break;
     }
 }
 
@@ -447,7 +614,39 @@ struct ImplNE {
             o32 ? launch<false, true>(h, fin, fout, p, s) : launch<false, false>(h, fin, fout, p, s);
         return hipGetLastError();
     }
-    static int steps_per_launch(const lbm_state_impl &, int) { return 1; }
+    // Several steps per launch on grids that fill the chip (see k_march_ne):
+    // from 2000 strip rows on, as for the other storages; below, the halo costs
+    // more than the launches.
+    static constexpr int kMost = ne_march_most<Sys, Lat>();
+    static int steps_per_launch(const lbm_state_impl &h, int want)
+    {
+        if (kMost < 2 || want < 2 || (long long)((h.nx + 61) / 62) * h.ny < 2000) return 1;
+        if ((long long)(h.nx + kTile) * Sys::K * Lat::Q * 2 >= 1ll << 31) return 1;   // a row's lane offsets
+        return want >= kMost && !(kMost == 3 && want == 4) ? kMost : 2;
+    }
+    template <int T>
+    static hipError_t launch_march(const lbm_state_impl &h, const void *fin, void *fout, hipStream_t s)
+    {
+        const KParams<float> p = h.kparams<float>(h.t0);
+        const int strips = march_strips(T, h.nx);
+        const int rows = march_rows(T, ne_march_lds<Sys, Lat>(T), Sys::K * Lat::Q, h.nx, h.ny);
+        const dim3 blocks((unsigned)(strips * ((h.ny + rows - 1) / rows)));
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, blocks, dim3(64), 0, s, gp(h, fin), mp(h, fin), (_Float16 *)fout,
+                               (float *)mp(h, fout), p, rows, strips);
+        };
+        h.field_b ? go(k_march_ne<Sys, Lat, T, true>) : go(k_march_ne<Sys, Lat, T, false>);
+        return hipGetLastError();
+    }
+    static hipError_t multi(const lbm_state_impl &h, int steps, const void *fin, void *fout, void *qhist, hipStream_t s)
+    {
+        if (qhist) return hipErrorInvalidValue;
+        if constexpr (kMost >= 2)
+            if (steps == 2) return launch_march<2>(h, fin, fout, s);
+        if constexpr (kMost > 2)
+            if (steps == kMost) return launch_march<kMost>(h, fin, fout, s);
+        return hipErrorInvalidValue;
+    }
     static hipError_t init(const lbm_state_impl &h, const double *Q, void *fout, double *speed, hipStream_t s)
     {
         hipLaunchKernelGGL((k_init_ne<Sys, Lat>), dim3(grid(h.C)), dim3(kBlock), 0, s, Q, (_Float16 *)fout,
@@ -489,7 +688,7 @@ struct ImplNE {
     }
     static const Launchers *get()
     {
-        static const Launchers L = {Sys::K, Lat::Q, Lat::D, 2, steps_per_launch, step, nullptr, init, init_absmax, moments,
+        static const Launchers L = {Sys::K, Lat::Q, Lat::D, 2, steps_per_launch, step, multi, init, init_absmax, moments,
                                     reduce, nullptr, nullptr, nullptr};
         return &L;
     }

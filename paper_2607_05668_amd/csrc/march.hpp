@@ -110,27 +110,26 @@ constexpr bool marches()
     return Lat::D == 2 && Sys::K <= 7 && 8 * march_lds<Sys, Lat, St>(2) <= kLdsPerCu;
 }
 
-// Rows of a wavefront's segment.  A wavefront of T stages collides
-// T rows + T (T - 1) rows, so few long segments cost least, but one wavefront
-// a SIMD is the least that fills the chip; a second one hides the latencies of
-// the first and costs 1.75 times its time in place of twice (up to 30
-// populations; 1.5 times with more).  Counts just above one or two wavefronts a
-// SIMD leave a SIMD with one more than the others: shallow water 512^2, four
-// stages, rows 3 / 4 / 6 (1539, 1152, 774 wavefronts): 7.4 / 8.0 / 7.1 us per
-// step.
+// Rows of a wavefront's segment.  A wavefront of T stages with `halo` lanes
+// and rows lost at each end collides T rows + T halo rows, so few long
+// segments cost least, but one wavefront a SIMD is the least that fills the
+// chip; a second one hides the latencies of the first and costs 1.75 times its
+// time in place of twice (up to 30 populations; 1.5 times with more).  Counts
+// just above one or two wavefronts a SIMD leave a SIMD with one more than the
+// others: shallow water 512^2, four stages, rows 3 / 4 / 6 (1539, 1152, 774
+// wavefronts): 7.4 / 8.0 / 7.1 us per step.
 constexpr int kSimds = 1024;
-template <class Sys, class Lat, class St>
-inline int march_rows(int T, int nx, int ny)
+inline int march_strips(int halo, int nx) { return (nx + 64 - 2 * halo - 1) / (64 - 2 * halo); }
+inline int march_rows(int halo, int lds, int populations, int nx, int ny)
 {
-    const int strips = (nx + 64 - 2 * (T - 1) - 1) / (64 - 2 * (T - 1));
-    const int two = std::min(2 * kSimds, kSimds / 4 * (kLdsPerCu / march_lds<Sys, Lat, St>(T)));
+    const int strips = march_strips(halo, nx), two = std::min(2 * kSimds, kSimds / 4 * (kLdsPerCu / lds));
     auto rows_for = [&](int waves) {
         const int segments = std::max(1, waves / strips);
         return (ny + segments - 1) / segments;
     };
     const int r1 = rows_for(kSimds), r2 = rows_for(two);
-    const double c1 = r1 + T - 1, c2 = (Sys::K * Lat::Q <= 30 ? 1.75 : 1.5) * (r2 + T - 1);
-    return c1 <= c2 ? r1 : r2;
+    const double c1 = r1 + halo, c2 = (populations <= 30 ? 1.75 : 1.5) * (r2 + halo);
+    return c1 <= c2 || two <= kSimds ? r1 : r2;
 }
 
 template <class Sys, class Lat, class St, int T, bool EXT, bool REC, int COLL>

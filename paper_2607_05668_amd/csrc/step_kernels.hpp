@@ -704,8 +704,8 @@ struct Impl {
     static void launch_march(const lbm_state_impl &h, const void *fin, void *fout, void *qhist, hipStream_t s)
     {
         const KParams<P> p = h.kparams<P>(h.t0);
-        const int strips = (h.nx + 64 - 2 * (T - 1) - 1) / (64 - 2 * (T - 1));
-        const int rows = march_rows<Sys, Lat, St>(T, h.nx, h.ny);
+        const int strips = march_strips(T - 1, h.nx);
+        const int rows = march_rows(T - 1, march_lds<Sys, Lat, St>(T), Sys::K * Lat::Q, h.nx, h.ny);
         hipLaunchKernelGGL((k_march<Sys, Lat, St, T, EXT, REC, COLL>), dim3((unsigned)(strips * ((h.ny + rows - 1) / rows))),
                            dim3(64), 0, s, (const St *)fin, (St *)fout, p, (R *)qhist, rows, strips);
     }
