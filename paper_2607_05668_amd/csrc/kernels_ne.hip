@@ -33,47 +33,6 @@ inline size_t ne_pop_bytes(long long C, int K, int Q)
     return (((size_t)K * Q * (size_t)padded_plane(C) * 2) + 255) & ~(size_t)255;
 }
 
-// element offset of deviation (k, i) of cell c (2D: c = y nx + x)
-template <int K, int Q>
-__device__ inline size_t ne_at(int k, int i, long long c)
-{
-    return (size_t)tile_offset<K, Q>(c) + (size_t)(k * Q + i) * kTile;
-}
-
-// Rebuild the pre-collision populations of cell (x, y, z) from the senders'
-// deviations and stored moments.
-template <class Sys, class Lat>
-__device__ inline void ne_load(const _Float16 *__restrict__ g, const float *__restrict__ M, const KParams<float> &p,
-                               const long long *src, float f[][Lat::Q])
-{
-    constexpr int K = Sys::K, Q = Lat::Q, D = Lat::D;
-    const size_t C = (size_t)p.C;
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        float My[K], ei[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) My[k] = M[(size_t)k * C + src[i]];
-        if (i == 0) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) ei[k] = ExactEq<Lat>::rest(My[k]);
-        } else {
-            float P[K][D];
-            Sys::template flux_delta<float, float>(p.phys, My, P);
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                float G[D], e[Q];
-#pragma unroll
-                for (int a = 0; a < D; ++a) G[a] = p.lam * P[k][a];
-                ExactEq<Lat>::feq(My[k], 0.0f, G, e);
-                ei[k] = e[i];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            f[k][i] = (float)g[ne_at<K, Q>(k, i, src[i])] * p.inv_scale[k] + ei[k];
-    }
-}
-
 // Collision of one cell from its pulled populations: emit(k, i, deviation in
 // the stored form, the cell's own equilibrium e_i); dQ: the moments.
 template <class Sys, class Lat, class Emit>
@@ -390,127 +349,183 @@ __global__ __launch_bounds__(64) void k_march_ne(const _Float16 *__restrict__ gi
     }
 }
 
-// Initial state: M(y) = Q(y) - Q0 rounded to float and, in the pull layout,
-// g_i(y) = f*eq_i(Q(y + c_i)) - e_i(M(y)) with the equilibrium of the
-// receiver's initial fields in double and e_i(M) as the step kernel forms it.
-template <class Sys, class Lat, bool STORE>
-__device__ inline void ne_init_cell(const double *__restrict__ Qin, const KParams<double> &pd,
-                                    const KParams<float> &pf, long long cell, _Float16 *g, float *M, double *mx)
+// A tile's halo senders for the kernels around the step: their equilibria's
+// parts in LDS (one flux evaluation per sender, as in k_step_ne), moment(k, c)
+// giving a cell's stored moments.  Ends with a barrier.
+constexpr int kNeHX = kNeTX + 2, kNeHY = kNeTY + 2, kNeHalo = kNeHX * kNeHY, kNeThreads = kNeTX * kNeTY;
+template <class Sys, class Lat, class Moment>
+__device__ __forceinline__ void ne_senders(const KParams<float> &p, int tx0, int ty0, float (*sP)[3][kNeHalo],
+                                           Moment &&moment)
 {
-    constexpr int K = Sys::K, Q = Lat::Q, D = Lat::D;
-    const size_t C = (size_t)pd.C;
-    int x, y, z;
-    cell_coords(cell, pd.nx, pd.ny, x, y, z);
-    long long dst[Q];
-    neighbours<Lat>(x, y, z, pd.nx, pd.ny, pd.nz, +1, dst);
-    float My[K];
+    constexpr int K = Sys::K, D = Lat::D;
+    for (int h = (int)threadIdx.x; h < kNeHalo; h += kNeThreads) {
+        const int hy = h / kNeHX, hx = h - hy * kNeHX;
+        const size_t c = (size_t)pmod(ty0 + hy - 1, p.ny) * p.nx + pmod(tx0 + hx - 1, p.nx);
+        float M[K], P[K][D];
 #pragma unroll
-    for (int k = 0; k < K; ++k) My[k] = (float)(Qin[(size_t)k * C + cell] - pd.phys.Q0[k]);
-    float Pm[K][D];
-    Sys::template flux_delta<float, float>(pf.phys, My, Pm);
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        // receiver's initial equilibrium in double
-        double dq[K], P[K][D];
-#pragma unroll
-        for (int k = 0; k < K; ++k) dq[k] = Qin[(size_t)k * C + dst[i]] - pd.phys.Q0[k];
-        Sys::template flux_delta<double, double>(pd.phys, dq, P);
+        for (int k = 0; k < K; ++k) M[k] = moment(k, c);
+        Sys::template flux_delta<float, float>(p.phys, M, P);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            double cd = 0.0;
+            float G[D], Pt[3];
 #pragma unroll
-            for (int a = 0; a < D; ++a) cd += lat_c<Lat>(i, a) * P[k][a];
-            const double feq = Lat::w[i] * (dq[k] + pd.lam_cs2 * cd);
-            float ei;
-            if (i == 0) {
-                ei = ExactEq<Lat>::rest(My[k]);
-            } else {
-                float G[D], e[Q];
+            for (int a = 0; a < D; ++a) G[a] = p.lam * P[k][a];
+            ExactEq<Lat>::parts(M[k], G, Pt);
 #pragma unroll
-                for (int a = 0; a < D; ++a) G[a] = pf.lam * Pm[k][a];
-                ExactEq<Lat>::feq(My[k], 0.0f, G, e);
-                ei = e[i];
-            }
-            const double gv = feq - (double)ei;
-            if constexpr (STORE)
-                g[ne_at<K, Q>(k, i, cell)] = (_Float16)(gv * (double)pf.scale[k]);
-            else
-                mx[k] = fabs(gv) > mx[k] ? fabs(gv) : mx[k];
+            for (int j = 0; j < 3; ++j) sP[k][j][h] = Pt[j];
         }
     }
-    if constexpr (STORE) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) M[(size_t)k * C + cell] = My[k];
-    }
+    __syncthreads();
 }
-
-template <class Sys, class Lat>
-__global__ __launch_bounds__(kBlock) void k_init_ne(const double *__restrict__ Qin, _Float16 *__restrict__ g,
-                                                    float *__restrict__ M, const KParams<double> pd,
-                                                    const KParams<float> pf)
+// e_i of the sender x - c_i, for the cell at (lx, ly) of the tile
+template <class Lat>
+__device__ __forceinline__ float ne_sent(const float (*sP)[kNeHalo], int lx, int ly, int i)
 {
-    const long long cell = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (cell >= pd.C) return;
-    ne_init_cell<Sys, Lat, true>(Qin, pd, pf, cell, g, M, nullptr);
+    const int h = (ly + 1 - Lat::cy[i]) * kNeHX + (lx + 1 - Lat::cx[i]);
+    const float Pt[3] = {sP[0][h], sP[1][h], sP[2][h]};
+    return i == 0 ? ExactEq<Lat>::rest_parts(Pt) : ExactEq<Lat>::dir(Pt, i);
 }
-
+// The moments of cell (x, y), summed in double from its rebuilt populations.
 template <class Sys, class Lat>
-__global__ __launch_bounds__(kBlock) void k_init_absmax_ne(const double *__restrict__ Qin, double *__restrict__ part,
-                                                           const KParams<double> pd, const KParams<float> pf)
-{
-    constexpr int K = Sys::K;
-    __shared__ double sh[kBlock / 64];
-    double mx[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) mx[k] = 0.0;
-    for (long long cell = (long long)blockIdx.x * kBlock + threadIdx.x; cell < pd.C;
-         cell += (long long)gridDim.x * kBlock)
-        ne_init_cell<Sys, Lat, false>(Qin, pd, pf, cell, nullptr, nullptr, mx);
-    for (int k = 0; k < K; ++k) {
-        const double r = block_reduce_max(mx[k], sh);
-        if (threadIdx.x == 0) part[(size_t)k * gridDim.x + blockIdx.x] = r;
-    }
-}
-
-template <class Sys, class Lat, class Out>
-__global__ __launch_bounds__(kBlock) void k_moments_ne(const _Float16 *__restrict__ g, const float *__restrict__ M,
-                                                       Out *__restrict__ out, const KParams<float> p,
-                                                       const KParams<double> pd, int absolute)
+__device__ __forceinline__ void ne_moments(const _Float16 *__restrict__ g, const KParams<float> &p,
+                                           const float (*sP)[3][kNeHalo], int x, int y, int lx, int ly, double *q)
 {
     constexpr int K = Sys::K, Q = Lat::Q;
-    const long long cell = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (cell >= p.C) return;
-    int x, y, z;
-    cell_coords(cell, p.nx, p.ny, x, y, z);
-    long long src[Q];
-    neighbours<Lat>(x, y, z, p.nx, p.ny, p.nz, -1, src);
-    float f[K][Q];
-    ne_load<Sys, Lat>(g, M, p, src, f);
+    size_t src[Q];
+    pulled_places<K, Lat, unsigned long long>((unsigned long long)y * p.nx + x, p.nx, p.ny, 1, src);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         double s = 0.0;
 #pragma unroll
-        for (int i = 0; i < Q; ++i) s += (double)f[k][i];
-        out[(size_t)k * (size_t)p.C + cell] = (Out)(absolute ? s + pd.phys.Q0[k] : s);
+        for (int i = 0; i < Q; ++i)
+            s += (double)fmaf((float)g[src[i] + (size_t)(k * Q * kTile)], p.inv_scale[k], ne_sent<Lat>(sP[k], lx, ly, i));
+        q[k] = s;
     }
 }
 
+// Initial state: M(y) = Q(y) - Q0 rounded to float and, in the pull layout,
+// g_i(y) = f*eq_i(Q(y + c_i)) - e_i(M(y)) with the equilibrium of the
+// receiver's initial fields in double and e_i(M) as the step kernel forms it.
+// A thread is a receiver: it forms its equilibrium once and writes what each of
+// its senders stores.  SCALE: only the largest |g| per field of the workgroup,
+// to part[k][block]; else the state, and where part is given the largest wave
+// speed of the workgroup, from the moments of the values as stored.
+// Neo-Hookean 2048^2: 363 + 524 us with the receivers' equilibria formed by
+// every sender, and 825 us for the speeds read back.
+template <class Sys, class Lat, bool SCALE>
+__global__ __launch_bounds__(kNeThreads) void k_init_ne(const double *__restrict__ Qin, _Float16 *__restrict__ g,
+                                                        float *__restrict__ M, double *__restrict__ part,
+                                                        const KParams<double> pd, const KParams<float> pf, unsigned tiles)
+{
+    constexpr int K = Sys::K, Q = Lat::Q, D = Lat::D;
+    __shared__ float sP[K][3][kNeHalo];
+    __shared__ double sh[kBlock / 64];
+    static_assert(kNeThreads == kBlock, "block reductions");
+    const size_t C = (size_t)pd.C;
+    const int tilesx = (pd.nx + kNeTX - 1) / kNeTX;
+    const int lx = (int)threadIdx.x % kNeTX, ly = (int)threadIdx.x / kNeTX;
+    double mx[K], fastest = 0.0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) mx[k] = 0.0;
+    for (unsigned t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const int tx0 = (int)(t % (unsigned)tilesx) * kNeTX, ty0 = (int)(t / (unsigned)tilesx) * kNeTY;
+        ne_senders<Sys, Lat>(pf, tx0, ty0, sP,
+                             [&](int k, size_t c) { return (float)(Qin[(size_t)k * C + c] - pd.phys.Q0[k]); });
+        const int x = tx0 + lx, y = ty0 + ly;
+        if (x < pd.nx && y < pd.ny) {
+            const size_t cell = (size_t)y * pd.nx + x;
+            double dq[K], P[K][D], q[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) dq[k] = Qin[(size_t)k * C + cell] - pd.phys.Q0[k];
+            Sys::template flux_delta<double, double>(pd.phys, dq, P);
+            size_t dst[Q];
+            pulled_places<K, Lat, unsigned long long>(cell, pd.nx, pd.ny, 1, dst);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                double s = 0.0;
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    double cd = 0.0;
+#pragma unroll
+                    for (int a = 0; a < D; ++a) cd += lat_c<Lat>(i, a) * P[k][a];
+                    const float ei = ne_sent<Lat>(sP[k], lx, ly, i);
+                    const double gv = Lat::w[i] * (dq[k] + pd.lam_cs2 * cd) - (double)ei;
+                    if constexpr (SCALE) {
+                        mx[k] = fabs(gv) > mx[k] ? fabs(gv) : mx[k];
+                    } else {
+                        const _Float16 v = (_Float16)(gv * (double)pf.scale[k]);
+                        g[dst[i] + (size_t)(k * Q * kTile)] = v;
+                        s += (double)fmaf((float)v, pf.inv_scale[k], ei);
+                    }
+                }
+                q[k] = s + pd.phys.Q0[k];
+                if constexpr (!SCALE) M[(size_t)k * C + cell] = (float)dq[k];
+            }
+            if constexpr (!SCALE) {
+                if (part) {
+                    const double v = Sys::template max_speed<double>(pd.phys, q);
+                    fastest = v > fastest ? v : fastest;
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if constexpr (SCALE) {
+        for (int k = 0; k < K; ++k) {
+            const double r = block_reduce_max(mx[k], sh);
+            if (threadIdx.x == 0) part[(size_t)k * gridDim.x + blockIdx.x] = r;
+        }
+    } else if (part) {
+        const double r = block_reduce_max(fastest, sh);
+        if (threadIdx.x == 0) part[blockIdx.x] = r;
+    }
+}
+
+template <class Sys, class Lat, class Out>
+__global__ __launch_bounds__(kNeThreads) void k_moments_ne(const _Float16 *__restrict__ g, const float *__restrict__ M,
+                                                           Out *__restrict__ out, const KParams<float> p,
+                                                           const KParams<double> pd, int absolute)
+{
+    constexpr int K = Sys::K;
+    __shared__ float sP[K][3][kNeHalo];
+    const size_t C = (size_t)p.C;
+    const int tilesx = (p.nx + kNeTX - 1) / kNeTX;
+    const unsigned t = (unsigned)xcd_tile(blockIdx.x, gridDim.x);
+    const int tx0 = (int)(t % (unsigned)tilesx) * kNeTX, ty0 = (int)(t / (unsigned)tilesx) * kNeTY;
+    const int lx = (int)threadIdx.x % kNeTX, ly = (int)threadIdx.x / kNeTX, x = tx0 + lx, y = ty0 + ly;
+    ne_senders<Sys, Lat>(p, tx0, ty0, sP, [&](int k, size_t c) { return M[(size_t)k * C + c]; });
+    if (x >= p.nx || y >= p.ny) return;
+    double q[K];
+    ne_moments<Sys, Lat>(g, p, sP, x, y, lx, ly, q);
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        out[(size_t)k * C + (size_t)y * p.nx + x] = (Out)(absolute ? q[k] + pd.phys.Q0[k] : q[k]);
+}
+
 template <class Sys, class Lat>
-__global__ __launch_bounds__(kBlock) void k_reduce1_ne(const _Float16 *__restrict__ g, const float *__restrict__ M,
-                                                       const double *__restrict__ ref, double *__restrict__ part,
-                                                       const KParams<float> p, const KParams<double> pd, int what)
+__global__ __launch_bounds__(kNeThreads) void k_reduce1_ne(const _Float16 *__restrict__ g, const float *__restrict__ M,
+                                                           const double *__restrict__ ref, double *__restrict__ part,
+                                                           const KParams<float> p, const KParams<double> pd, int what,
+                                                           unsigned tiles)
 {
     constexpr int K = Sys::K, Q = Lat::Q;
+    __shared__ float sP[K][3][kNeHalo];
     __shared__ double sh[kBlock / 64];
     const size_t C = (size_t)p.C;
     const unsigned nb = gridDim.x;
     if (what == 4) {
+        // a wavefront takes a tile of deviations, a lane one cell; then the
+        // moments (the padding of the last tile is never read)
         double cnt = 0.0;
-        // deviations in the tile-blocked layout; the padding of the last tile is never read
-        const size_t n = (size_t)K * Q * (size_t)padded_plane((long long)C);
-        for (size_t j = (size_t)blockIdx.x * kBlock + threadIdx.x; j < n; j += (size_t)nb * kBlock) {
-            if ((j / ((size_t)K * Q * kTile)) * kTile + j % kTile >= C) continue;
-            cnt += isfinite((float)g[j]) ? 0.0 : 1.0;
+        const size_t T = (C + kTile - 1) / kTile, waves = (size_t)nb * (kBlock / 64);
+        for (size_t t = (size_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); t < T; t += waves) {
+            const unsigned lane = threadIdx.x & 63u;
+            if (t * kTile + lane >= C) continue;
+            const _Float16 *cell = g + t * (size_t)(K * Q * kTile) + lane;
+            int bad = 0;
+#pragma unroll
+            for (int j = 0; j < K * Q; ++j) bad += isfinite((float)cell[(size_t)j * kTile]) ? 0 : 1;
+            cnt += bad;
         }
         for (size_t j = (size_t)blockIdx.x * kBlock + threadIdx.x; j < (size_t)K * C; j += (size_t)nb * kBlock)
             cnt += isfinite(M[j]) ? 0.0 : 1.0;
@@ -518,46 +533,45 @@ __global__ __launch_bounds__(kBlock) void k_reduce1_ne(const _Float16 *__restric
         if (threadIdx.x == 0) part[blockIdx.x] = r;
         return;
     }
+    const int tilesx = (p.nx + kNeTX - 1) / kNeTX;
+    const int lx = (int)threadIdx.x % kNeTX, ly = (int)threadIdx.x / kNeTX;
     double a0[K], a1[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) a0[k] = a1[k] = 0.0;
-    for (long long cell = (long long)blockIdx.x * kBlock + threadIdx.x; cell < p.C; cell += (long long)nb * kBlock) {
-        int x, y, z;
-        cell_coords(cell, p.nx, p.ny, x, y, z);
-        long long src[Q];
-        neighbours<Lat>(x, y, z, p.nx, p.ny, p.nz, -1, src);
-        float f[K][Q];
-        ne_load<Sys, Lat>(g, M, p, src, f);
-        double q[K];
+    for (unsigned t = blockIdx.x; t < tiles; t += nb) {
+        const int tx0 = (int)(t % (unsigned)tilesx) * kNeTX, ty0 = (int)(t / (unsigned)tilesx) * kNeTY;
+        const int x = tx0 + lx, y = ty0 + ly;
+        ne_senders<Sys, Lat>(p, tx0, ty0, sP, [&](int k, size_t c) { return M[(size_t)k * C + c]; });
+        if (x < p.nx && y < p.ny) {
+            const size_t cell = (size_t)y * p.nx + x;
+            double q[K];
+            ne_moments<Sys, Lat>(g, p, sP, x, y, lx, ly, q);
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            double s = 0.0;
+            for (int k = 0; k < K; ++k) q[k] += pd.phys.Q0[k];
+            if (what == 0) {
 #pragma unroll
-            for (int i = 0; i < Q; ++i) s += (double)f[k][i];
-            q[k] = s + pd.phys.Q0[k];
-        }
-        if (what == 0) {
+                for (int k = 0; k < K; ++k) a0[k] += q[k];
+            } else if (what == 1) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) a0[k] += q[k];
-        } else if (what == 1) {
+                for (int k = 0; k < K; ++k) {
+                    const double r = ref[(size_t)k * C + cell];
+                    a0[k] += (q[k] - r) * (q[k] - r);
+                    a1[k] += r * r;
+                }
+            } else if (what == 2) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const double r = ref[(size_t)k * C + cell];
-                a0[k] += (q[k] - r) * (q[k] - r);
-                a1[k] += r * r;
+                for (int k = 0; k < K; ++k) {
+                    const double r = ref[(size_t)k * C + cell];
+                    const double e = fabs(q[k] - r);
+                    a0[k] = e > a0[k] ? e : a0[k];
+                    a1[k] = fabs(r) > a1[k] ? fabs(r) : a1[k];
+                }
+            } else {
+                const double sp = Sys::template max_speed<double>(pd.phys, q);
+                a0[0] = sp > a0[0] ? sp : a0[0];
             }
-        } else if (what == 2) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const double r = ref[(size_t)k * C + cell];
-                const double e = fabs(q[k] - r);
-                a0[k] = e > a0[k] ? e : a0[k];
-                a1[k] = fabs(r) > a1[k] ? fabs(r) : a1[k];
-            }
-        } else {
-            const double sp = Sys::template max_speed<double>(pd.phys, q);
-            a0[0] = sp > a0[0] ? sp : a0[0];
         }
+        __syncthreads();
     }
     const int nslot = (what == 3) ? 1 : (what == 0 ? K : 2 * K);
     for (int j = 0; j < nslot; ++j) {
@@ -571,7 +585,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce2_ne(const double *__restrict_
                                                        int nslot, int nb, int is_max)
 {
     __shared__ double sh[kBlock / 64];
-    for (int j = 0; j < nslot; ++j) {
+    for (int j = blockIdx.x; j < nslot; j += gridDim.x) {
         double v = 0.0;
         for (int b = threadIdx.x; b < nb; b += kBlock) {
             const double w = part[(size_t)j * nb + b];
@@ -584,7 +598,6 @@ __global__ __launch_bounds__(kBlock) void k_reduce2_ne(const double *__restrict_
 
 template <class Sys, class Lat>
 struct ImplNE {
-    static unsigned grid(long long C) { return (unsigned)((C + kBlock - 1) / kBlock); }
     static unsigned step_grid(const lbm_state_impl &h)
     {
         return (unsigned)(((h.nx + kNeTX - 1) / kNeTX) * (long long)((h.ny + kNeTY - 1) / kNeTY));
@@ -647,19 +660,25 @@ struct ImplNE {
             if (steps == kMost) return launch_march<kMost>(h, fin, fout, s);
         return hipErrorInvalidValue;
     }
+    static void combine(double *part, int nslot, unsigned nb, int is_max, hipStream_t s)
+    {
+        hipLaunchKernelGGL(k_reduce2_ne, dim3(nslot), dim3(kBlock), 0, s, part, part + (size_t)2 * LBM_MAXK * kRedBlocks,
+                           nslot, (int)nb, is_max);
+    }
     static hipError_t init(const lbm_state_impl &h, const double *Q, void *fout, double *speed, hipStream_t s)
     {
-        hipLaunchKernelGGL((k_init_ne<Sys, Lat>), dim3(grid(h.C)), dim3(kBlock), 0, s, Q, (_Float16 *)fout,
-                           (float *)mp(h, fout), h.kparams<double>(h.t0), h.kparams<float>(h.t0));
-        const hipError_t e = hipGetLastError();
-        return e != hipSuccess || !speed ? e : reduce(h, fout, 3, nullptr, speed, s);
+        const unsigned nb = std::min(step_grid(h), (unsigned)kInitBlocks);
+        hipLaunchKernelGGL((k_init_ne<Sys, Lat, false>), dim3(nb), dim3(kNeThreads), 0, s, Q, (_Float16 *)fout,
+                           (float *)mp(h, fout), speed, h.kparams<double>(h.t0), h.kparams<float>(h.t0), step_grid(h));
+        if (speed) combine(speed, 1, nb, 1, s);
+        return hipGetLastError();
     }
     static hipError_t init_absmax(const lbm_state_impl &h, const double *Q, double *part, hipStream_t s)
     {
-        hipLaunchKernelGGL((k_init_absmax_ne<Sys, Lat>), dim3(kRedBlocks), dim3(kBlock), 0, s, Q, part,
-                           h.kparams<double>(h.t0), h.kparams<float>(h.t0));
-        hipLaunchKernelGGL(k_reduce2_ne, dim3(1), dim3(kBlock), 0, s, part, part + (size_t)2 * LBM_MAXK * kRedBlocks,
-                           Sys::K, kRedBlocks, 1);
+        const unsigned nb = std::min(step_grid(h), (unsigned)(2 * kRedBlocks));
+        hipLaunchKernelGGL((k_init_ne<Sys, Lat, true>), dim3(nb), dim3(kNeThreads), 0, s, Q, (_Float16 *)nullptr,
+                           (float *)nullptr, part, h.kparams<double>(h.t0), h.kparams<float>(h.t0), step_grid(h));
+        combine(part, Sys::K, nb, 1, s);
         return hipGetLastError();
     }
     static hipError_t moments(const lbm_state_impl &h, const void *fin, void *out, int absolute, int out_dtype,
@@ -668,22 +687,22 @@ struct ImplNE {
         const KParams<float> p = h.kparams<float>(h.t0);
         const KParams<double> pd = h.kparams<double>(h.t0);
         if (out_dtype == 0)
-            hipLaunchKernelGGL((k_moments_ne<Sys, Lat, double>), dim3(grid(h.C)), dim3(kBlock), 0, s, gp(h, fin),
+            hipLaunchKernelGGL((k_moments_ne<Sys, Lat, double>), dim3(step_grid(h)), dim3(kNeThreads), 0, s, gp(h, fin),
                                mp(h, fin), (double *)out, p, pd, absolute);
         else
-            hipLaunchKernelGGL((k_moments_ne<Sys, Lat, float>), dim3(grid(h.C)), dim3(kBlock), 0, s, gp(h, fin),
+            hipLaunchKernelGGL((k_moments_ne<Sys, Lat, float>), dim3(step_grid(h)), dim3(kNeThreads), 0, s, gp(h, fin),
                                mp(h, fin), (float *)out, p, pd, absolute);
         return hipGetLastError();
     }
     static hipError_t reduce(const lbm_state_impl &h, const void *fin, int what, const double *ref, double *aux,
                              hipStream_t s)
     {
-        hipLaunchKernelGGL((k_reduce1_ne<Sys, Lat>), dim3(kRedBlocks), dim3(kBlock), 0, s, gp(h, fin), mp(h, fin), ref,
-                           aux, h.kparams<float>(h.t0), h.kparams<double>(h.t0), what);
         const int nslot = (what == 3 || what == 4) ? 1 : (what == 0 ? Sys::K : 2 * Sys::K);
         const int is_max = (what == 2 || what == 3) ? 1 : 0;
-        hipLaunchKernelGGL(k_reduce2_ne, dim3(1), dim3(kBlock), 0, s, aux, aux + (size_t)2 * LBM_MAXK * kRedBlocks,
-                           nslot, kRedBlocks, is_max);
+        const unsigned nb = std::min(step_grid(h), (unsigned)std::min(2 * kRedBlocks, 2 * LBM_MAXK * kRedBlocks / nslot));
+        hipLaunchKernelGGL((k_reduce1_ne<Sys, Lat>), dim3(nb), dim3(kNeThreads), 0, s, gp(h, fin), mp(h, fin), ref, aux,
+                           h.kparams<float>(h.t0), h.kparams<double>(h.t0), what, step_grid(h));
+        combine(aux, nslot, nb, is_max, s);
         return hipGetLastError();
     }
     static const Launchers *get()
