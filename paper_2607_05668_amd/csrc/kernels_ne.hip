@@ -228,9 +228,6 @@ __global__ __launch_bounds__(64) void k_march_ne(const _Float16 *__restrict__ gi
     int xw = xo % p.nx;
     xw = xw < 0 ? xw + p.nx : xw;
     const size_t C = (size_t)p.C;
-    auto rsrc = [](const void *base) {
-        return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, 0x7fffffff, 0x00027000);
-    };
     int yn = (y0 - HALO) % p.ny;                                          // the row that stage 0 loads next
     yn = yn < 0 ? yn + p.ny : yn;
     const int last = y1 - y0 + 2 * HALO - 1;
@@ -240,9 +237,9 @@ __global__ __launch_bounds__(64) void k_march_ne(const _Float16 *__restrict__ gi
     auto load = [&](_Float16 (&gt)[K][Q], float (&mt)[K], bool more) {
         const size_t c = (size_t)yn * (size_t)p.nx;
         const unsigned off = tile_offset<K, Q>((unsigned)(c % kTile) + (unsigned)xw) * 2u;
-        const auto rg = rsrc(gin + c / kTile * (size_t)(K * Q * kTile));
+        const auto rg = rsrc_of(gin + c / kTile * (size_t)(K * Q * kTile));
 #pragma unroll
-        for (int k = 0; k < K; ++k) mt[k] = ld_buf<float>(rsrc(Min + k * C + c), (unsigned)xw * 4u, 0);
+        for (int k = 0; k < K; ++k) mt[k] = ld_buf<float>(rsrc_of(Min + k * C + c), (unsigned)xw * 4u, 0);
 #pragma unroll
         for (int k = 0; k < K; ++k)
 #pragma unroll
@@ -306,12 +303,12 @@ __global__ __launch_bounds__(64) void k_march_ne(const _Float16 *__restrict__ gi
             if (s == T - 1) {                                             // rows y0 to y1 only: none wraps
                 const size_t c = (size_t)yu * (size_t)p.nx;
                 const unsigned off = mine ? tile_offset<K, Q>((unsigned)(c % kTile) + (unsigned)xw) * 2u : 0x80000000u;
-                const auto rg = rsrc(gout + c / kTile * (size_t)(K * Q * kTile));
+                const auto rg = rsrc_of(gout + c / kTile * (size_t)(K * Q * kTile));
                 ne_collide<Sys, Lat>(p, f, bl, dQ, [&](int k, int i, _Float16 v, float) {
                     st_masked(rg, off, (k * Q + i) * kTile * 2, v);
                 });
 #pragma unroll
-                for (int k = 0; k < K; ++k) st_masked(rsrc(Mout + k * C + c), mine ? (unsigned)xw * 4u : 0x80000000u, 0, dQ[k]);
+                for (int k = 0; k < K; ++k) st_masked(rsrc_of(Mout + k * C + c), mine ? (unsigned)xw * 4u : 0x80000000u, 0, dQ[k]);
             } else {
                 ne_collide<Sys, Lat>(p, f, bl, dQ, [&](int k, int i, _Float16 v, float e) {
                     post[k][i] = fmaf((float)v, p.inv_scale[k], e);
