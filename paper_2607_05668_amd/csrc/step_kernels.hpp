@@ -475,20 +475,23 @@ inline unsigned reduce_blocks(long long C, int nslot)
 // the transpose of d post / d f of eq. (lbe_update) (every population of a
 // field enters the collision only through Q_k).  The Jacobian products come
 // from one forward-mode pass with K tangents.
-template <class Sys, class Lat, class R>
+// I: byte offsets within a plane, 32-bit where one fits 4 GiB (scalar plane
+// base + lane offset, as the step kernels address their slabs).
+template <class Sys, class Lat, class R, class I>
 __global__ __launch_bounds__(kBlock) void k_adj_step(const R *__restrict__ lin, R *__restrict__ lout,
                                                      const R *__restrict__ qh, R *__restrict__ grad_b,
                                                      const KParams<R> p)
 {
     constexpr int K = Sys::K, Q = Lat::Q, D = Lat::D;
     using DK = Dual<R, K>;
-    const long long cell = xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
-    if (cell >= p.C) return;
+    const I cell = (I)xcd_tile(blockIdx.x, gridDim.x) * kBlock + threadIdx.x;
+    if (cell >= (I)p.C) return;
     int x, y, z;
-    cell_coords(cell, p.nx, p.ny, x, y, z);
-    long long src[Q];
-    neighbours<Lat>(x, y, z, p.nx, p.ny, p.nz, +1, src);
+    cell_coords<I>(cell, p.nx, p.ny, x, y, z);
+    I src[Q];
+    neighbours<Lat, I>(x, y, z, p.nx, p.ny, p.nz, +1, src);
     const size_t C = (size_t)p.C;
+    const I own = cell * (I)sizeof(R);
     // This cell's moments and coefficients are loaded first, then the pulled
     // adjoint populations: the load counter retires in issue order, so the
     // Jacobian below waits only for the moments while the populations are
@@ -496,19 +499,27 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R *__restrict__ lin, 
     DK dQ[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        dQ[k] = DK(qh[(size_t)k * C + cell]);
+        dQ[k] = DK(*byte_at(qh + (size_t)k * C, own));
         dQ[k].d[k] = R(1);
     }
     R bl[3] = {R(0), R(0), R(0)};
     if (p.b) {
 #pragma unroll
-        for (int a = 0; a < D; ++a) bl[a] = ((const R *)p.b)[(size_t)a * C + cell];
+        for (int a = 0; a < D; ++a) bl[a] = *byte_at((const R *)p.b + (size_t)a * C, own);
     }
     R mu[K][Q], M0[K], M1[K][D];
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
-        for (int i = 0; i < Q; ++i) mu[k][i] = lin[(size_t)(k * Q + i) * C + src[i]];
+        for (int i = 0; i < Q; ++i) mu[k][i] = *byte_at(lin + (size_t)(k * Q + i) * C, src[i] * (I)sizeof(R));
+    // the topography gradient so far comes along, not after the last store
+    const bool topo = Sys::id == SYS_SWE && grad_b && p.b;
+    R gb[2] = {R(0), R(0)};
+    if (topo) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) gb[a] = *byte_at(grad_b + (size_t)a * C, own);
+    }
+    __builtin_amdgcn_sched_barrier(0);
     DK dPhi[K][D], Sk[K];
     Sys::template flux_delta<DK, R>(p.phys, dQ, dPhi);
     // M0_k = sum_i w_i mu_{k,i} and L1_{k,a} = (lam/cs2) sum_i w_i c_ia mu_{k,i},
@@ -555,14 +566,16 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R *__restrict__ lin, 
         const R del = p.delta[k];
 #pragma unroll
         for (int i = 0; i < Q; ++i)
-            lout[(size_t)(k * Q + i) * C + cell] = (R(2) * M0[k] - mu[k][i]) - del * (M0[k] - mu[k][i]) + F[k];
+            *byte_at(lout + (size_t)(k * Q + i) * C, own) =
+                (R(2) * M0[k] - mu[k][i]) - del * (M0[k] - mu[k][i]) + F[k];
     }
     if constexpr (Sys::id == SYS_SWE) {
-        if (grad_b && p.b) {
+        if (topo) {
             // S_hu_a = -g h b_a  =>  dL/db_a += dt M0_{hu_a} (-g h)
-            const R h = qh[cell] + p.phys.Q0[0];
+            const R h = dQ[0].v + p.phys.Q0[0];
 #pragma unroll
-            for (int a = 0; a < 2; ++a) grad_b[(size_t)a * C + cell] += p.dt * M0[1 + a] * (-p.phys.g * h);
+            for (int a = 0; a < 2; ++a)
+                *byte_at(grad_b + (size_t)a * C, own) = gb[a] + p.dt * M0[1 + a] * (-p.phys.g * h);
         }
     }
 }
@@ -806,8 +819,12 @@ struct Impl {
                                hipStream_t s)
     {
         const KParams<R> p = h.kparams<R>(h.t0);
-        hipLaunchKernelGGL((k_adj_step<Sys, Lat, R>), dim3(grid(h.C)), dim3(kBlock), 0, s, (const R *)lin, (R *)lout,
-                           (const R *)qhist, (R *)gb, p);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(grid(h.C)), dim3(kBlock), 0, s, (const R *)lin, (R *)lout, (const R *)qhist,
+                               (R *)gb, p);
+        };
+        fits_o32(h.C, 1, sizeof(R)) && fits_i32(h.C) ? go(k_adj_step<Sys, Lat, R, unsigned>)
+                                                     : go(k_adj_step<Sys, Lat, R, unsigned long long>);
         return hipGetLastError();
     }
     static hipError_t adj_init(const lbm_state_impl &h, const void *lam0, const double *Q, double *dQ0, hipStream_t s)
