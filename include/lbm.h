@@ -250,8 +250,10 @@ int lbm_set_field(lbm_state *h, const char *name, const void *dev_ptr);
  * Returns LBM_ESUBCHAR if (dt/dx) max |eig A_n| exceeds cs (Sec. 2.4.2). */
 int lbm_init_moments(lbm_state *h, const double *Q_dev);
 
-/* Advance n collide-and-stream steps (eq. lbe_update), one fused kernel per
- * step with pull streaming between the A/B buffers.  Asynchronous, unless
+/* Advance n collide-and-stream steps (eq. lbe_update), fused kernels with pull
+ * streaming between the A/B buffers.  Consecutive steps of 2D grids share
+ * launches, up to four steps in each; the populations are bit for bit those of
+ * n calls with one step.  Asynchronous, unless
  * check_every is set (see lbm_set_param): then LBM_ENONFINITE reports
  * non-finite populations. */
 int lbm_step(lbm_state *h, int n);

@@ -3,22 +3,21 @@
 // storage).  Included by one translation unit per system family
 // (sys_*.hip), which the build compiles in parallel.
 //
-// Memory layout: structure of arrays, z-slab major: population (k, i) of
-// cell (x, y, z) at [z][k][i][y][x] (for 2D grids [k][i][cells]), x fastest,
-// so each wavefront of 64 lanes touches 64 consecutive cells of one
-// population (fully coalesced).  A/B buffers with pull streaming: buffer P
-// holds the post-collision populations of the previous step, and the
-// pre-collision population of cell x is P_i(x - c_i) (periodic wrap), so
-// every population crosses HBM once read and once written per step and all
-// stores are aligned.
+// Memory layout: tiles of 64 cells of a z-slab, each holding its populations
+// (k, i) one after another, x fastest, so each wavefront of 64 lanes touches
+// 64 consecutive cells of one population (fully coalesced).  A/B buffers with
+// pull streaming: buffer P holds the post-collision populations of the
+// previous step, and the pre-collision population of cell x is P_i(x - c_i)
+// (periodic wrap).
 //
-// One thread updates one cell: load K*Q populations (a1), moments (a2),
-// fluctuation-form flux (a3), shifted equilibrium (a4), sources (a5), BGK
-// relaxation (a6), aligned store (a7) -- eq. (moments), (feq) with the
-// Sec. 2.5.2 shift, and (lbe_update).  The workgroup index is remapped so
-// that consecutive tiles of cells run on the same XCD (the hardware
-// dispatches workgroups round-robin over the 8 XCDs, each with its own L2),
-// keeping the rows that neighbouring tiles share in one L2.
+// k_step advances one step: one thread updates one cell, loading its K*Q
+// populations (a1), colliding them (a2 to a6, collide.hpp) and storing them
+// aligned (a7), so every population is read once and written once per step.
+// Runs of two steps and more in 2D take the kernel of march.hpp instead, which
+// does so once for up to four steps.  The workgroup index of k_step is
+// remapped so that consecutive tiles of cells run on the same XCD (the
+// hardware dispatches workgroups round-robin over the 8 XCDs, each with its
+// own L2), keeping the rows that neighbouring tiles share in one L2.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -154,7 +153,8 @@ __device__ inline void nsf_mms_source(const MmsParams<R> &m, const Phys<R> &p, R
 // Workgroup size of the step kernel.  The 17-field cascade keeps ~250
 // values live per cell: a 512-thread workgroup (two waves per SIMD) caps a
 // wave at 256 of the SIMD's 512 registers per lane, so two waves share each
-// SIMD and one hides the other's loads (in FP32 it needs 230, no spills).
+// SIMD and one hides the other's loads (in FP32 it needs 252, no spills; 256^3:
+// 2780 us per step, 2797 and 2778 with 128 and 256 threads).
 // In FP64 the largest states (12 fields and more) need more than 256 even
 // so and would spill to scratch; a 256-thread workgroup lets one wave per
 // SIMD keep the overflow in accumulation registers instead (resistive MHD
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(kBlock) void k_init(const double *__restrict__ Qin,
 #pragma unroll
                 for (int a = 0; a < D; ++a) cd += lat_c<Lat>(i, a) * dPhi[k][a];
                 const double feq = Lat::w[i] * (dQ[k] + p.lam_cs2 * cd);
-                const St v = (St)(feq * (double)p.scale[k]);
+                const St v = stored_of<St>(feq * (double)p.scale[k]);
                 fout[dst[i] + (size_t)(k * Q * kTile)] = v;
                 s += (double)v;
             }
