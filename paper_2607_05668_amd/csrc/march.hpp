@@ -70,7 +70,7 @@ struct RowFields {
 template <class T>
 __device__ __forceinline__ void st_masked(__amdgpu_buffer_rsrc_t r, unsigned off, int base, T v)
 {
-        constexpr int aux = 0;
+    constexpr int aux = 0;
     if constexpr (sizeof(T) == 8) {
         typedef int v2 __attribute__((ext_vector_type(2)));
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2, v), r, off, base, aux);
@@ -312,5 +312,100 @@ __global__ __launch_bounds__(64) void k_march(const St *__restrict__ fin, St *__
         if (j == last) break;
         row(all, odd, j + 1);
         if (j + 1 == last) break;
+    }
+}
+
+// ---------------------------------------------------------- small grids ----
+// On a grid that leaves most of the chip idle a step's time is the launch and
+// one cell's chain of loads and arithmetic.  Here a workgroup takes a square of
+// kSquare^2 cells, one per thread (a wavefront per SIMD), through `steps`
+// steps: the populations pass between the threads through LDS, and the middle
+// cells of the square, steps - 1 away from its edge, are stored (after t steps
+// a cell t - 1 away from the edge is right; the others hold what is used by
+// nobody).
+//
+// Bound: latency.  A launch takes about 3 us beside its steps (kernel start,
+// addresses, loads from the other XCDs' results, stores) and a step 1 us (a
+// double chain of about 400 instructions of one wavefront, LDS, two barriers).
+// us per step with 1 (k_step) / 2 / 3 / 4 / 5 / 6 / 7 steps a launch: shallow
+// water 64^2, D2Q9, float 2.9 / 2.53 / 2.04 / 1.75 / 1.52 / 1.52 / 1.44;
+// advection-diffusion 64^2, D2Q5, double 3.2 / 2.68 / 2.26 / 2.05 / 1.84 /
+// 1.88 / 1.85.
+constexpr int kSquare = 16;
+constexpr int kSquareMost = 5;
+inline int square_out(int steps) { return kSquare - 2 * (steps - 1); }
+// Whether a square's moving populations fit 64 KiB of LDS.
+template <class Sys, class Lat, class St>
+constexpr bool squares()
+{
+    return marches<Sys, Lat, St>()
+           && (Sys::K * (Lat::Q - 1) * kSquare * kSquare + 2 * (kSquare + 1)) * (int)sizeof(St) <= 64 * 1024;
+}
+
+template <class Sys, class Lat, class St, bool EXT, bool REC, int COLL>
+__global__ __launch_bounds__(kSquare * kSquare) void k_square(const St *__restrict__ fin, St *__restrict__ fout,
+                                                              const KParams<typename Cell<Sys, Lat, St, COLL>::P> p,
+                                                              typename Store<St>::R *__restrict__ qhist, int steps,
+                                                              int across)
+{
+    using C = Cell<Sys, Lat, St, COLL>;
+    using F = typename Store<St>::R;
+    constexpr int K = Sys::K, Q = Lat::Q, W = kSquare, N = W * W;
+    const int halo = steps - 1, out = W - 2 * halo;
+    const int tid = (int)threadIdx.x, lx = tid % W, ly = tid / W;
+    const int xu = ((int)blockIdx.x % across) * out - halo + lx, yu = ((int)blockIdx.x / across) * out - halo + ly;
+    const bool mine = lx >= halo && lx < W - halo && ly >= halo && ly < W - halo && xu < p.nx && yu < p.ny;
+    int x = xu % p.nx, y = yu % p.ny;
+    x = x < 0 ? x + p.nx : x;
+    y = y < 0 ? y + p.ny : y;
+    const unsigned cell = (unsigned)y * (unsigned)p.nx + (unsigned)x;
+    F f[K][Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        const int xs = wrapi(x - Lat::cx[i], p.nx), ys = wrapi(y - Lat::cy[i], p.ny);
+        const unsigned off = tile_offset<K, Q>((unsigned)ys * (unsigned)p.nx + (unsigned)xs) * (unsigned)sizeof(St);
+#pragma unroll
+        for (int k = 0; k < K; ++k) f[k][i] = Store<St>::ld(byte_at(fin + (k * Q + i) * kTile, off));
+    }
+    constexpr int NB = CoefTraits<Sys>::NB > 0 ? CoefTraits<Sys>::NB : 1;
+    F cf[NB];
+    if (EXT && p.b) {
+#pragma unroll
+        for (int a = 0; a < CoefTraits<Sys>::NB; ++a) cf[a] = ((const F *)p.b)[a * (size_t)p.C + cell];
+    }
+    const RowFields<F, EXT> ex = {cf, (const F *)p.sext, (size_t)p.C, (size_t)cell};
+    __shared__ St mid[K * (Q - 1) * N + 2 * (W + 1)];                     // a neighbour's word is in bounds for every thread
+    St *const here = &mid[W + 1 + tid];
+    St post[K][Q];
+    for (int s = 0;; ++s) {
+        F dQ[K];
+        C::update(p, f, ex, nullptr, dQ, [&](int k, int i, St v) { post[k][i] = v; });
+        if constexpr (REC) {
+            if (mine) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) qhist[(s * (size_t)K + k) * (size_t)p.C + cell] = dQ[k];
+            }
+        }
+        if (s == halo) break;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int i = 1; i < Q; ++i) here[(k * (Q - 1) + i - 1) * N] = post[k][i];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            f[k][0] = (F)post[k][0];
+#pragma unroll
+            for (int i = 1; i < Q; ++i)
+                f[k][i] = (F)here[(k * (Q - 1) + i - 1) * N - Lat::cx[i] - W * Lat::cy[i]];
+        }
+        __syncthreads();
+    }
+    if (mine) {
+        const unsigned own = tile_offset<K, Q>(cell) * (unsigned)sizeof(St);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int i = 0; i < Q; ++i) *byte_at(fout + (k * Q + i) * kTile, own) = post[k][i];
     }
 }

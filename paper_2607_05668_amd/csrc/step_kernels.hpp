@@ -693,19 +693,37 @@ struct Impl {
                : launch_step<false, false, COLL_BGK>(h, fin, fout, qhist, s, p);
         return hipGetLastError();
     }
-    // ---- several steps per launch (k_march) ----
+    // ---- several steps per launch (k_march, k_square) ----
     static constexpr bool kMarch = marches<Sys, Lat, St>();
     static constexpr int kMost = kMarch ? march_most<Sys, Lat, St>() : 1;
-    // Steps of the next launch when `want` are left (1: k_step).  A grid of at
-    // most 700 strip rows (wavefronts of one row each) takes two steps a
-    // launch: the launch costs as much as the arithmetic of a row, and SIMDs
-    // are free for the halo (shallow water 64^2: 2.93 -> 2.60 us per step, 150
-    // x 101: 3.11 -> 2.86).  Up to 2000 strip rows the chip has no room for
+    // Steps per launch of k_square on a small grid (0: not for this grid): five
+    // or four, the most that leaves a CU at most one square; with two a CU the
+    // cells computed twice cost more than a launch (us per step, best other
+    // route / four / five: shallow water 150 x 101 2.77 / 2.26 / 2.14, 160^2
+    // 2.83 / 2.73 / 2.60, 256^2 3.73 / 3.69 / 3.63; Euler 150 x 101 2.34 / 1.90
+    // / 1.78; neo-Hookean 150^2 4.72 / 3.70 / 4.34; advection-diffusion in
+    // double 128^2 3.28 / 2.68 / 2.21, 256^2 4.19 / 4.72 / 5.07).
+    static int square_steps(const lbm_state_impl &h)
+    {
+        if constexpr (squares<Sys, Lat, St>()) {
+            for (int steps = kSquareMost; steps >= 4; --steps) {
+                const long long out = square_out(steps);
+                if (((h.nx + out - 1) / out) * ((h.ny + out - 1) / out) <= kSimds / 4) return steps;
+            }
+        }
+        return 0;
+    }
+    // Steps of the next launch when `want` are left (1: k_step).  Small grids
+    // take k_square.  Else a grid of at most 700 strip rows (wavefronts of one
+    // row each) takes two steps a launch: the launch costs as much as the
+    // arithmetic of a row, and SIMDs are free for the halo (shallow water 64^2:
+    // 2.93 -> 2.60 us per step, 150 x 101: 3.11 -> 2.86).  Up to 2000 strip rows the chip has no room for
     // the halo (256^2: one step 3.77, two 4.10, three 4.02 us); beyond, fewer
     // passes over memory pay (384^2: 6.0 -> 5.3, 512^2: 9.3 -> 7.0).
     static int steps_per_launch(const lbm_state_impl &h, int want)
     {
         if (!kMarch || want < 2 || h.regularized) return 1;
+        if (const int most = square_steps(h)) return std::min(most, want);
         // a row's lane offsets stay below 2^31 bytes
         if ((long long)(h.nx + kTile) * Sys::K * Lat::Q * (long long)sizeof(St) >= 1ll << 31) return 1;
         const long long strip_rows = (long long)((h.nx + 61) / 62) * h.ny;
@@ -742,8 +760,39 @@ struct Impl {
         }
         return hipGetLastError();
     }
+    template <bool EXT, bool REC, int COLL>
+    static void launch_square(const lbm_state_impl &h, int steps, const void *fin, void *fout, void *qhist, hipStream_t s)
+    {
+        const KParams<P> p = h.kparams<P>(h.t0);
+        const int out = square_out(steps), across = (h.nx + out - 1) / out, up = (h.ny + out - 1) / out;
+        hipLaunchKernelGGL((k_square<Sys, Lat, St, EXT, REC, COLL>), dim3((unsigned)(across * up)),
+                           dim3(kSquare * kSquare), 0, s, (const St *)fin, (St *)fout, p, (R *)qhist, steps, across);
+    }
+    static hipError_t launch_square(const lbm_state_impl &h, int steps, const void *fin, void *fout, void *qhist,
+                                    hipStream_t s)
+    {
+        const bool ext = h.field_b || h.field_src;
+        if (qhist) {
+            if constexpr (Sys::K <= 6) {
+                if (h.trt_lambda > 0) return hipErrorInvalidValue;       // the moment history serves the BGK adjoint
+                launch_square<true, true, COLL_BGK>(h, steps, fin, fout, qhist, s);
+            } else {
+                return hipErrorInvalidValue;
+            }
+        } else if (h.trt_lambda > 0) {
+            launch_square<true, false, COLL_TRT>(h, steps, fin, fout, nullptr, s);
+        } else if (ext) {
+            launch_square<true, false, COLL_BGK>(h, steps, fin, fout, nullptr, s);
+        } else {
+            launch_square<false, false, COLL_BGK>(h, steps, fin, fout, nullptr, s);
+        }
+        return hipGetLastError();
+    }
     static hipError_t multi(const lbm_state_impl &h, int steps, const void *fin, void *fout, void *qhist, hipStream_t s)
     {
+        if constexpr (squares<Sys, Lat, St>())
+            if (const int most = square_steps(h))
+                return steps >= 1 && steps <= most ? launch_square(h, steps, fin, fout, qhist, s) : hipErrorInvalidValue;
         if constexpr (kMarch) {
             if (steps == 2) return launch_march<2>(h, fin, fout, qhist, s);
             if constexpr (kMost > 2)

@@ -135,3 +135,21 @@ def test_two_relaxation_times_in_several_steps_per_launch(system, lattice, stora
         for _ in range(9):
             b.step(1)
         assert torch.equal(populations(a), populations(b)), shape
+
+
+# squares of 16 x 16 cells store 8 x 8 of them after five steps, 10 x 10 after
+# four: one square, a ragged second one, the largest grids of 256 squares and
+# the first beyond
+@pytest.mark.parametrize("shape", [(8, 8), (9, 17), (128, 128), (129, 128), (160, 160), (160, 161)])
+@pytest.mark.parametrize("system,lattice,storage", [("swe2d", "D2Q9", "f32"), ("advdiff_trk2d", "D2Q5", "f64"),
+                                                    ("neohooke2d", "D2Q9", "f16"), ("nse_trk2d", "D2Q5", "f32")])
+def test_small_grids_in_several_steps_per_launch(system, lattice, storage, shape):
+    a, b = make(system, lattice, storage, shape), make(system, lattice, storage, shape)
+    for s in (a, b):
+        s.init(initial(system, shape))
+    for n in (2, 4, 5, 13):
+        a.step(n)
+        for _ in range(n):
+            b.step(1)
+        assert torch.isfinite(a.moments()).all()
+        assert torch.equal(populations(a), populations(b)), n
