@@ -18,6 +18,10 @@ update over the kernel's average launch duration: HIP events on the stream
 the kernel runs on bracket the K back-to-back launches), the FP64 CPU oracle on a
 bounded sample of the same workload, and the adjoint/forward time ratio of
 the checkpointed shallow-water rollout (512^2, 500 steps, snapshot every 50).
+
+2D runs share launches between steps, so the algorithmic_GBps of the extra 2D
+workloads (2*K*Q*sizeof bytes per cell and step over the time) counts bytes
+that do not cross HBM and can exceed its rate.
 """
 import argparse
 import hashlib

@@ -324,13 +324,15 @@ __global__ __launch_bounds__(64) void k_march(const St *__restrict__ fin, St *__
 // a cell t - 1 away from the edge is right; the others hold what is used by
 // nobody).
 //
-// Bound: latency.  A launch takes about 3 us beside its steps (kernel start,
-// addresses, loads from the other XCDs' results, stores) and a step 1 us (a
-// double chain of about 400 instructions of one wavefront, LDS, two barriers).
-// us per step with 1 (k_step) / 2 / 3 / 4 / 5 / 6 / 7 steps a launch: shallow
-// water 64^2, D2Q9, float 2.9 / 2.53 / 2.04 / 1.75 / 1.52 / 1.52 / 1.44;
-// advection-diffusion 64^2, D2Q5, double 3.2 / 2.68 / 2.26 / 2.05 / 1.84 /
-// 1.88 / 1.85.
+// Bound: latency.  A launch takes about 2.5 us beside its steps (kernel start,
+// addresses, loads, stores) and a step 1 us (a double chain of about 400
+// instructions of one wavefront, LDS, two barriers).  Neighbouring squares run
+// on one XCD, so that most of a square's loads hit the L2 that the last launch
+// wrote (in dispatch order: 150 x 101 2.13 against 1.65 us per step, 160^2 2.72
+// against 1.70).  us per step with 1 (k_step) / 2 / 3 / 4 / 5 / 6 / 7 steps a
+// launch: shallow water 64^2, D2Q9, float 2.9 / 2.35 / 1.89 / 1.64 / 1.43 /
+// 1.43 / 1.39; advection-diffusion 64^2, D2Q5, double 3.2 / 2.56 / 2.14 / 1.91
+// / 1.72 / 1.70 / 1.67.
 constexpr int kSquare = 16;
 constexpr int kSquareMost = 5;
 inline int square_out(int steps) { return kSquare - 2 * (steps - 1); }
@@ -353,7 +355,8 @@ __global__ __launch_bounds__(kSquare * kSquare) void k_square(const St *__restri
     constexpr int K = Sys::K, Q = Lat::Q, W = kSquare, N = W * W;
     const int halo = steps - 1, out = W - 2 * halo;
     const int tid = (int)threadIdx.x, lx = tid % W, ly = tid / W;
-    const int xu = ((int)blockIdx.x % across) * out - halo + lx, yu = ((int)blockIdx.x / across) * out - halo + ly;
+    const int g = (int)xcd_tile(blockIdx.x, gridDim.x);
+    const int xu = g % across * out - halo + lx, yu = g / across * out - halo + ly;
     const bool mine = lx >= halo && lx < W - halo && ly >= halo && ly < W - halo && xu < p.nx && yu < p.ny;
     int x = xu % p.nx, y = yu % p.ny;
     x = x < 0 ? x + p.nx : x;

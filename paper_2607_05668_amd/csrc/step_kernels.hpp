@@ -696,20 +696,32 @@ struct Impl {
     // ---- several steps per launch (k_march, k_square) ----
     static constexpr bool kMarch = marches<Sys, Lat, St>();
     static constexpr int kMost = kMarch ? march_most<Sys, Lat, St>() : 1;
-    // Steps per launch of k_square on a small grid (0: not for this grid): five
-    // or four, the most that leaves a CU at most one square; with two a CU the
-    // cells computed twice cost more than a launch (us per step, best other
-    // route / four / five: shallow water 150 x 101 2.77 / 2.26 / 2.14, 160^2
-    // 2.83 / 2.73 / 2.60, 256^2 3.73 / 3.69 / 3.63; Euler 150 x 101 2.34 / 1.90
-    // / 1.78; neo-Hookean 150^2 4.72 / 3.70 / 4.34; advection-diffusion in
-    // double 128^2 3.28 / 2.68 / 2.21, 256^2 4.19 / 4.72 / 5.07).
+    // Steps per launch of k_square on a small grid (0: not for this grid).  Per
+    // step a launch costs its 3 us over the steps and a step about 1 us where a
+    // CU has at most one square, 0.55 us more for each further one: the count
+    // with the least sum.  More steps store less of a square and make more of
+    // them.  Beyond four squares of three steps a CU the cells computed twice
+    // cost as much as the marching kernel's passes over memory.  us per step,
+    // other route / three / four / five steps: shallow water 150 x 101 2.78 /
+    // 2.04 / 1.74 / 1.66, 200^2 3.40 / 2.58 / 2.21 / 2.49, 256^2 3.78 / 2.83 /
+    // 2.83 / 3.00, 384^2 5.26 / 4.44 / 4.51 / 5.35, 512^2 6.67 / 6.42 / 6.89 /
+    // 8.66; Euler 300^2 3.79 / 2.71 / 2.73 / 3.29; advection-diffusion in double
+    // 192^2 3.76 / 2.41 / 2.95 / 3.57, 384^2 7.55 / 5.75 / 6.89 / 8.76;
+    // neo-Hookean 200^2 4.95 / 4.59 / 4.10 / 5.19, 256^2 5.71 / 5.29 / 5.83 / 6.42.
     static int square_steps(const lbm_state_impl &h)
     {
         if constexpr (squares<Sys, Lat, St>()) {
-            for (int steps = kSquareMost; steps >= 4; --steps) {
+            constexpr double cus = kSimds / 4;
+            int best = 0;
+            double least = 0;
+            for (int steps = 3; steps <= kSquareMost; ++steps) {
                 const long long out = square_out(steps);
-                if (((h.nx + out - 1) / out) * ((h.ny + out - 1) / out) <= kSimds / 4) return steps;
+                const double n = (double)((h.nx + out - 1) / out) * (double)((h.ny + out - 1) / out);
+                if (steps == 3 && n > 4 * cus) return 0;
+                const double cost = 3.0 / steps + 0.55 * std::max(0.0, n / cus - 1);
+                if (!best || cost < least) best = steps, least = cost;
             }
+            return best;
         }
         return 0;
     }

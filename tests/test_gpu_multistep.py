@@ -138,9 +138,10 @@ def test_two_relaxation_times_in_several_steps_per_launch(system, lattice, stora
 
 
 # squares of 16 x 16 cells store 8 x 8 of them after five steps, 10 x 10 after
-# four: one square, a ragged second one, the largest grids of 256 squares and
-# the first beyond
-@pytest.mark.parametrize("shape", [(8, 8), (9, 17), (128, 128), (129, 128), (160, 160), (160, 161)])
+# four, 12 x 12 after three: one square, a ragged second one, grids on both
+# sides of the changes from five to four to three steps and to other kernels
+@pytest.mark.parametrize("shape", [(8, 8), (9, 17), (128, 128), (129, 128), (160, 160), (192, 192), (200, 200),
+                                   (384, 384), (384, 385)])
 @pytest.mark.parametrize("system,lattice,storage", [("swe2d", "D2Q9", "f32"), ("advdiff_trk2d", "D2Q5", "f64"),
                                                     ("neohooke2d", "D2Q9", "f16"), ("nse_trk2d", "D2Q5", "f32")])
 def test_small_grids_in_several_steps_per_launch(system, lattice, storage, shape):
