@@ -252,7 +252,7 @@ int lbm_init_moments(lbm_state *h, const double *Q_dev);
 
 /* Advance n collide-and-stream steps (eq. lbe_update), fused kernels with pull
  * streaming between the A/B buffers.  Consecutive steps of 2D grids share
- * launches, up to four steps in each; the populations are bit for bit those of
+ * launches, up to five steps in each; the populations are bit for bit those of
  * n calls with one step.  Asynchronous, unless
  * check_every is set (see lbm_set_param): then LBM_ENONFINITE reports
  * non-finite populations. */

@@ -26,8 +26,9 @@ SYSTEMS = {
     "neohooke2d": ("acoustic", 0.1, 20.0, None, {"rho0": 1.0, "mu_s": 1.0, "lambda_s": 2.0}, [1, 0, 0, 1, 0, 0]),
     "gen_euler2d": ("acoustic", 0.05, 5.0, None, {}, [1, 3, 3, 1 / (1.4 * 0.4) + 9]),
 }
-# at most 700 strips' rows (62 columns each) two steps a launch, from 2000 on
-# the most steps a launch, in between one: the last four are of the large kind
+# up to 1024 squares of 12 x 12 cells the squares; else (thin grids, states too
+# large for them) at most 700 strips' rows (62 columns each) two steps a launch,
+# from 2000 on the most steps a launch, in between one
 SHAPES = [(1, 1), (2, 3), (130, 1), (1, 130), (61, 59), (40, 60), (9, 62), (70, 64), (33, 121), (101, 150), (40, 1200),
           (2100, 30), (3, 43400), (210, 640), (67, 2011)]
 
@@ -154,3 +155,42 @@ def test_small_grids_in_several_steps_per_launch(system, lattice, storage, shape
             b.step(1)
         assert torch.isfinite(a.moments()).all()
         assert torch.equal(populations(a), populations(b)), n
+
+
+# beyond 1024 squares of 12 x 12: the marching kernel, ragged strips and segments
+@pytest.mark.parametrize("shape", [(397, 411), (1201, 130)])
+@pytest.mark.parametrize("trt", [0.0, 3.0 / 16.0])
+@pytest.mark.parametrize("system,lattice,storage", [("swe2d", "D2Q9", "f32"), ("euler2d", "D2Q5", "f64"),
+                                                    ("neohooke2d", "D2Q9", "f16"), ("nse_trk2d", "D2Q5", "f32")])
+def test_large_grids_in_several_steps_per_launch(system, lattice, storage, trt, shape):
+    a, b = (make(system, lattice, storage, shape, trt_lambda=trt) for _ in range(2))
+    for s in (a, b):
+        s.init(initial(system, shape))
+    for n in (2, 3, 4, 11):
+        a.step(n)
+        for _ in range(n):
+            b.step(1)
+        assert torch.equal(populations(a), populations(b)), n
+
+
+@pytest.mark.parametrize("shape", [(397, 411), (1201, 130)])
+@pytest.mark.parametrize("storage", ["f32", "f64", "f16"])
+def test_fields_and_history_of_large_grids_in_several_steps_per_launch(storage, shape):
+    a, b = make("swe2d", "D2Q9", storage, shape), make("swe2d", "D2Q9", storage, shape)
+    rng = np.random.default_rng(5)
+    src = 0.01 * rng.standard_normal((a.K,) + shape)
+    top = 0.01 * rng.standard_normal((2,) + shape)
+    for s in (a, b):
+        s.set_field("grad_zb", top)
+        s.set_field("source", src)
+        s.init(initial("swe2d", shape))
+    a.step(6)
+    for _ in range(6):
+        b.step(1)
+    ha = torch.full((7, a.K) + shape, float("nan"), dtype=a.real, device="cuda")
+    hb = torch.empty_like(ha)
+    a.step_record(7, ha)
+    for j in range(7):
+        b.step_record(1, hb[j])
+    assert torch.equal(ha, hb)
+    assert torch.equal(populations(a), populations(b))
