@@ -630,8 +630,8 @@ struct ImplNE {
     static constexpr int kMost = ne_march_most<Sys, Lat>();
     static int steps_per_launch(const lbm_state_impl &h, int want)
     {
-        if (kMost < 2 || want < 2 || (long long)((h.nx + 61) / 62) * h.ny < 2000) return 1;
-        if ((long long)(h.nx + kTile) * Sys::K * Lat::Q * 2 >= 1ll << 31) return 1;   // a row's lane offsets
+        if (kMost < 2 || want < 2 || !march_row_fits(h.nx, Sys::K * Lat::Q, 2)) return 1;
+        if ((long long)((h.nx + 61) / 62) * h.ny < 2000) return 1;
         return want >= kMost && !(kMost == 3 && want == 4) ? kMost : 2;
     }
     template <int T>

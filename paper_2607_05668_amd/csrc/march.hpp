@@ -23,9 +23,10 @@
 // cost 18 us at three stages, misaligned loads nothing).
 #pragma once
 
-#include <algorithm>
-
 #include "collide.hpp"
+#include "march_plan.hpp"
+
+static_assert(kTile == kMarchLanes, "a strip is a tile wide");
 
 // The value of lane l - 1 (C = +1) or l + 1 (C = -1); zero past the ends.
 template <int C>
@@ -47,8 +48,8 @@ __device__ __forceinline__ F lane_pull(F v, int i)      // i a constant after un
     return Lat::cx[i] > 0 ? lane_pull<1>(v) : (Lat::cx[i] < 0 ? lane_pull<-1>(v) : v);
 }
 
-// Buffer descriptor of the 2 GiB from base on: offsets at and beyond 2^31 are
-// out of range for every access.
+// Buffer descriptor of the 2^31 - 1 bytes from base on (march_row_fits keeps a
+// row within them): offsets at and beyond 2^31 are out of range for every access.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void *base)
 {
     return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, 0x7fffffff, 0x00027000);
@@ -111,7 +112,6 @@ constexpr int march_lds(int T) { return ((T - 1) * march_slots<Lat>() * Sys::K *
 // a CU their LDS, else three or two.  Shallow water 2048^2, D2Q9, float, us
 // per step: 152 one step per launch, 120, 86, 61 two, three and four; five
 // (five wavefronts a CU) 66.
-constexpr int kLdsPerCu = 160 * 1024;
 template <class Sys, class Lat, class St>
 constexpr int march_most()
 {
@@ -126,28 +126,6 @@ template <class Sys, class Lat, class St>
 constexpr bool marches()
 {
     return Lat::D == 2 && Sys::K <= 7 && 8 * march_lds<Sys, Lat, St>(2) <= kLdsPerCu;
-}
-
-// Rows of a wavefront's segment.  A wavefront of T stages with `halo` lanes
-// and rows lost at each end collides T rows + T halo rows, so few long
-// segments cost least, but one wavefront a SIMD is the least that fills the
-// chip; a second one hides the latencies of the first and costs 1.75 times its
-// time in place of twice (up to 30 populations; 1.5 times with more).  Counts
-// just above one or two wavefronts a SIMD leave a SIMD with one more than the
-// others: shallow water 512^2, four stages, rows 3 / 4 / 6 (1539, 1152, 774
-// wavefronts): 7.4 / 8.0 / 7.1 us per step.
-constexpr int kSimds = 1024;
-inline int march_strips(int halo, int nx) { return (nx + 64 - 2 * halo - 1) / (64 - 2 * halo); }
-inline int march_rows(int halo, int lds, int populations, int nx, int ny)
-{
-    const int strips = march_strips(halo, nx), two = std::min(2 * kSimds, kSimds / 4 * (kLdsPerCu / lds));
-    auto rows_for = [&](int waves) {
-        const int segments = std::max(1, waves / strips);
-        return (ny + segments - 1) / segments;
-    };
-    const int r1 = rows_for(kSimds), r2 = rows_for(two);
-    const double c1 = r1 + halo, c2 = (populations <= 30 ? 1.75 : 1.5) * (r2 + halo);
-    return c1 <= c2 || two <= kSimds ? r1 : r2;
 }
 
 template <class Sys, class Lat, class St, int T, bool EXT, bool REC, int COLL>

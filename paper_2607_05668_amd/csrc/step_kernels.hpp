@@ -736,8 +736,7 @@ struct Impl {
     {
         if (!kMarch || want < 2 || h.regularized) return 1;
         if (const int most = square_steps(h)) return std::min(most, want);
-        // a row's lane offsets stay below 2^31 bytes
-        if ((long long)(h.nx + kTile) * Sys::K * Lat::Q * (long long)sizeof(St) >= 1ll << 31) return 1;
+        if (!march_row_fits(h.nx, Sys::K * Lat::Q, sizeof(St))) return 1;
         const long long strip_rows = (long long)((h.nx + 61) / 62) * h.ny;
         if (strip_rows <= 700) return 2;
         if (strip_rows < 2000) return 1;

@@ -1,0 +1,47 @@
+"""Host arithmetic of the marching kernels' launches (csrc/march_plan.hpp),
+compiled by the host compiler and checked against direct enumeration."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2607_05668_amd", "csrc")
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+
+
+def run(tmp_path, body):
+    """Compile body as main() with the header; undefined arithmetic ends the program."""
+    src = tmp_path / "plan.cpp"
+    src.write_text('#include <cstdio>\n#include "march_plan.hpp"\nint main()\n{\n' + body + "\n    return 0;\n}\n")
+    exe = str(tmp_path / "plan")
+    cc = subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-I" + CSRC,
+                         str(src), "-o", exe], capture_output=True, text=True, timeout=120)
+    assert cc.returncode == 0, cc.stderr[-4000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+def test_rows_taken_lie_within_the_descriptor(tmp_path):
+    """Around the limit of every field count, lattice and element size: a row
+    that march_row_fits takes ends within 2^31 - 1 bytes of its first tile, from
+    whichever cell of the tile it begins, and nothing is refused that is more
+    than two tiles below the limit."""
+    out = run(tmp_path, r"""
+    for (int q : {5, 9})
+        for (int k = 1; k <= 18; ++k)
+            for (int e : {2, 4, 8}) {
+                const long long bytes = (long long)k * q * e, top = 0x7fffffff / bytes;
+                for (long long nx = top - 400; nx <= top + 10; ++nx) {
+                    const bool fits = march_row_fits(nx, k * q, e);
+                    for (long long b = 0; b < 64; ++b) {
+                        const long long end = ((b + nx - 1) / 64 + 1) * 64 * bytes;
+                        if (fits && end > 0x7fffffff) { printf("nx %lld first cell %lld, %lld bytes a cell\n", nx, b, bytes); return 1; }
+                    }
+                    if (!fits && nx < top - 200) { printf("refused nx %lld, %lld bytes a cell\n", nx, bytes); return 1; }
+                }
+            }
+    puts("ok");""")
+    assert out == "ok\n"
