@@ -222,7 +222,7 @@ __global__ __launch_bounds__(64) void k_march_ne(const _Float16 *__restrict__ gi
     const int lane = (int)threadIdx.x;
     const unsigned g = (unsigned)xcd_tile(blockIdx.x, gridDim.x);
     const int strip = (int)(g % (unsigned)strips);
-    const int y0 = (int)(g / (unsigned)strips) * rows, y1 = y0 + rows < p.ny ? y0 + rows : p.ny;
+    const int y0 = (int)(g / (unsigned)strips) * rows, y1 = segment_end(y0, rows, p.ny);
     const int xo = strip * (64 - 2 * HALO) + lane - HALO;                 // unwrapped column
     const bool mine = lane >= HALO && lane < 64 - HALO && xo < p.nx;      // column stored by this lane
     int xw = xo % p.nx;
@@ -630,7 +630,7 @@ struct ImplNE {
     static constexpr int kMost = ne_march_most<Sys, Lat>();
     static int steps_per_launch(const lbm_state_impl &h, int want)
     {
-        if (kMost < 2 || want < 2 || !march_row_fits(h.nx, Sys::K * Lat::Q, 2)) return 1;
+        if (kMost < 2 || want < 2 || !march_fits(h.nx, h.ny, Sys::K * Lat::Q, 2)) return 1;
         if ((long long)((h.nx + 61) / 62) * h.ny < 2000) return 1;
         return want >= kMost && !(kMost == 3 && want == 4) ? kMost : 2;
     }
@@ -640,7 +640,7 @@ struct ImplNE {
         const KParams<float> p = h.kparams<float>(h.t0);
         const int strips = march_strips(T, h.nx);
         const int rows = march_rows(T, ne_march_lds<Sys, Lat>(T), Sys::K * Lat::Q, h.nx, h.ny);
-        const dim3 blocks((unsigned)(strips * ((h.ny + rows - 1) / rows)));
+        const dim3 blocks((unsigned)(strips * march_segments(h.ny, rows)));
         auto go = [&](auto kern) {
             hipLaunchKernelGGL(kern, blocks, dim3(64), 0, s, gp(h, fin), mp(h, fin), (_Float16 *)fout,
                                (float *)mp(h, fout), p, rows, strips);

@@ -48,7 +48,7 @@ __device__ __forceinline__ F lane_pull(F v, int i)      // i a constant after un
     return Lat::cx[i] > 0 ? lane_pull<1>(v) : (Lat::cx[i] < 0 ? lane_pull<-1>(v) : v);
 }
 
-// Buffer descriptor of the 2^31 - 1 bytes from base on (march_row_fits keeps a
+// Buffer descriptor of the 2^31 - 1 bytes from base on (march_fits keeps a
 // row within them): offsets at and beyond 2^31 are out of range for every access.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void *base)
 {
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(64) void k_march(const St *__restrict__ fin, St *__
     const int lane = (int)threadIdx.x;                                    // one wavefront per workgroup
     const unsigned g = (unsigned)xcd_tile(blockIdx.x, gridDim.x);
     const int strip = (int)(g % (unsigned)strips);
-    const int y0 = (int)(g / (unsigned)strips) * rows, y1 = y0 + rows < p.ny ? y0 + rows : p.ny;
+    const int y0 = (int)(g / (unsigned)strips) * rows, y1 = segment_end(y0, rows, p.ny);
     const int xo = strip * WOUT + lane - HALO;                            // unwrapped column
     const bool mine = lane >= HALO && lane < 64 - HALO && xo < p.nx;      // column stored by this lane
     int xw = xo % p.nx;

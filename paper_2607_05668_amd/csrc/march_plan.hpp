@@ -8,15 +8,21 @@ constexpr int kMarchLanes = 64;         // lanes of a wavefront, cells of a popu
 constexpr int kSimds = 1024;
 constexpr int kLdsPerCu = 160 * 1024;
 
-// Whether every population of a row lies in the 2^31 - 1 bytes that a buffer
-// descriptor at the row's first tile covers (offsets beyond are refused by its
-// range check).  The row begins up to 63 cells into that tile, its last cell
-// lies in tile (63 + nx - 1) / 64 at most, and that tile's last population ends
-// with the tile: (nx + 126) populations' bytes.
-constexpr bool march_row_fits(long long nx, int populations, int elem)
+// Grids whose addresses and row numbers the marching kernels hold.  Every
+// population of a row lies in the 2^31 - 1 bytes that a buffer descriptor at
+// the row's first tile covers (offsets beyond are refused by its range check):
+// the row begins up to 63 cells into that tile, its last cell lies in tile
+// (63 + nx - 1) / 64 at most, and that tile's last population ends with the
+// tile: (nx + 126) populations' bytes.  Unwrapped row numbers run past ny by
+// the halo.
+constexpr bool march_fits(long long nx, long long ny, int populations, int elem)
 {
-    return (nx + 2 * kMarchLanes) * populations * elem <= 0x7fffffff;
+    return (nx + 2 * kMarchLanes) * populations * elem <= 0x7fffffff && ny <= 0x7fffffff - kMarchLanes;
 }
+
+// Segments of `rows` rows, and the row at which the one from y0 on ends.
+constexpr int march_segments(int ny, int rows) { return (ny - 1) / rows + 1; }
+constexpr int segment_end(int y0, int rows, int ny) { return ny - y0 < rows ? ny : y0 + rows; }
 
 // Rows of a wavefront's segment.  A wavefront of T stages with `halo` lanes
 // and rows lost at each end collides T rows + T halo rows, so few long
@@ -31,8 +37,7 @@ inline int march_rows(int halo, int lds, int populations, int nx, int ny)
 {
     const int strips = march_strips(halo, nx), two = std::min(2 * kSimds, kSimds / 4 * (kLdsPerCu / lds));
     auto rows_for = [&](int waves) {
-        const int segments = std::max(1, waves / strips);
-        return (ny + segments - 1) / segments;
+        return (ny - 1) / std::max(1, waves / strips) + 1;
     };
     const int r1 = rows_for(kSimds), r2 = rows_for(two);
     const double c1 = r1 + halo, c2 = (populations <= 30 ? 1.75 : 1.5) * (r2 + halo);

@@ -736,7 +736,7 @@ struct Impl {
     {
         if (!kMarch || want < 2 || h.regularized) return 1;
         if (const int most = square_steps(h)) return std::min(most, want);
-        if (!march_row_fits(h.nx, Sys::K * Lat::Q, sizeof(St))) return 1;
+        if (!march_fits(h.nx, h.ny, Sys::K * Lat::Q, sizeof(St))) return 1;
         const long long strip_rows = (long long)((h.nx + 61) / 62) * h.ny;
         if (strip_rows <= 700) return 2;
         if (strip_rows < 2000) return 1;
@@ -748,7 +748,7 @@ struct Impl {
         const KParams<P> p = h.kparams<P>(h.t0);
         const int strips = march_strips(T - 1, h.nx);
         const int rows = march_rows(T - 1, march_lds<Sys, Lat, St>(T), Sys::K * Lat::Q, h.nx, h.ny);
-        hipLaunchKernelGGL((k_march<Sys, Lat, St, T, EXT, REC, COLL>), dim3((unsigned)(strips * ((h.ny + rows - 1) / rows))),
+        hipLaunchKernelGGL((k_march<Sys, Lat, St, T, EXT, REC, COLL>), dim3((unsigned)(strips * march_segments(h.ny, rows))),
                            dim3(64), 0, s, (const St *)fin, (St *)fout, p, (R *)qhist, rows, strips);
     }
     template <int T>

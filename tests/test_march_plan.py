@@ -26,7 +26,7 @@ def run(tmp_path, body):
 
 def test_rows_taken_lie_within_the_descriptor(tmp_path):
     """Around the limit of every field count, lattice and element size: a row
-    that march_row_fits takes ends within 2^31 - 1 bytes of its first tile, from
+    that march_fits takes ends within 2^31 - 1 bytes of its first tile, from
     whichever cell of the tile it begins, and nothing is refused that is more
     than two tiles below the limit."""
     out = run(tmp_path, r"""
@@ -35,7 +35,7 @@ def test_rows_taken_lie_within_the_descriptor(tmp_path):
             for (int e : {2, 4, 8}) {
                 const long long bytes = (long long)k * q * e, top = 0x7fffffff / bytes;
                 for (long long nx = top - 400; nx <= top + 10; ++nx) {
-                    const bool fits = march_row_fits(nx, k * q, e);
+                    const bool fits = march_fits(nx, 1, k * q, e);
                     for (long long b = 0; b < 64; ++b) {
                         const long long end = ((b + nx - 1) / 64 + 1) * 64 * bytes;
                         if (fits && end > 0x7fffffff) { printf("nx %lld first cell %lld, %lld bytes a cell\n", nx, b, bytes); return 1; }
@@ -43,5 +43,29 @@ def test_rows_taken_lie_within_the_descriptor(tmp_path):
                     if (!fits && nx < top - 200) { printf("refused nx %lld, %lld bytes a cell\n", nx, bytes); return 1; }
                 }
             }
+    puts("ok");""")
+    assert out == "ok\n"
+
+
+def test_segments_cover_every_row_once(tmp_path):
+    """Rows of a segment, the number of segments and their ends, up to the
+    tallest grids an int holds: consecutive, none empty, the last one ends with
+    the grid (the sanitizer ends the program on an overflow)."""
+    out = run(tmp_path, r"""
+    const int most = 0x7fffffff - kMarchLanes;
+    for (int ny : {1, 2, 3, 64, 1023, 1024, 1025, 2048, 43400, 1 << 20, 1 << 30, (1 << 30) + 1, most - 1024, most - 1, most})
+        for (int nx : {1, 2, 56, 57, 58, 59, 64, 150, 1024, 2048, 130001})
+            for (int halo = 1; halo <= 4; ++halo)
+                for (int lds : {2568, 7688, 20744, 30728})
+                    for (int populations : {5, 27, 63}) {
+                        const int rows = march_rows(halo, lds, populations, nx, ny), n = march_segments(ny, rows);
+                        bool ok = rows >= 1 && n >= 1 && (long long)(n - 1) * rows < ny && (long long)n * rows >= ny;
+                        for (int g : {0, n / 2, n - 2, n - 1}) {
+                            if (!ok || g < 0) continue;
+                            const int y0 = g * rows, y1 = segment_end(y0, rows, ny);
+                            ok = y1 > y0 && y1 <= ny && (g == n - 1 ? y1 == ny : y1 == y0 + rows);
+                        }
+                        if (!ok) { printf("%d rows of %d, halo %d: %d segments of %d\n", ny, nx, halo, n, rows); return 1; }
+                    }
     puts("ok");""")
     assert out == "ok\n"
