@@ -253,7 +253,11 @@ int lbm_init_moments(lbm_state *h, const double *Q_dev);
 /* Advance n collide-and-stream steps (eq. lbe_update), fused kernels with pull
  * streaming between the A/B buffers.  Consecutive steps of 2D grids share
  * launches, up to five steps in each; the populations are bit for bit those of
- * n calls with one step.  Asynchronous, unless
+ * n calls with one step.  Every launch swaps the two buffers, so which of them
+ * holds the current populations follows from the launches and not from the
+ * step count (lbm_snapshot copies the current ones).  While the caller captures
+ * the bound stream into a graph, an even n ends in the buffer that it began
+ * with, so that the graph can be replayed.  Asynchronous, unless
  * check_every is set (see lbm_set_param): then LBM_ENONFINITE reports
  * non-finite populations. */
 int lbm_step(lbm_state *h, int n);

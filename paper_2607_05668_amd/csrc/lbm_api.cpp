@@ -242,10 +242,19 @@ GraphCache &graphs(lbm_state *h)
     return *(GraphCache *)h->graphs;
 }
 
+// Whether the caller is capturing the bound stream: the launches then go into
+// the caller's graph one by one (a graph of the handle's own would be replayed
+// outside of it).
+bool capturing(const lbm_state *h)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return h->stream && hipStreamIsCapturing(h->stream, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+
 bool batch_launches(const lbm_state *h, int n)
 {
     return h->use_graphs && n >= kGraphMinLaunches && h->C <= kGraphMaxCells &&
-           !(h->sys == SYS_NSF17 && h->mms_on) && h->check_every == 0;
+           !(h->sys == SYS_NSF17 && h->mms_on) && h->check_every == 0 && !capturing(h);
 }
 
 // Replay the graph of `key`, capturing it first with enqueue(stream) if it
@@ -766,11 +775,28 @@ static int check_finite(lbm_state *h)
 }
 
 // Enqueue `left` steps on s, as few launches as the kernels allow, alternating
-// the population buffers from cur on; counts left down.
-static hipError_t enqueue_steps(lbm_state *h, int &left, char *qhist, size_t stride, int &cur, hipStream_t s)
+// the population buffers from cur on; counts left down.  A captured run keeps
+// the buffers in the order of single steps (an even number of steps ends in the
+// buffer that it began with), or a replay would not go on from the last one's
+// state: each launch of an even number of steps swaps the buffers once where
+// its steps would not, so if there is an odd number of them, one runs in two
+// halves.
+static hipError_t enqueue_steps(lbm_state *h, int &left, char *qhist, size_t stride, int &cur, hipStream_t s,
+                                bool captured)
 {
-    while (left > 0) {
-        const int m = h->L->steps_per_launch(*h, left);
+    bool halve = false;
+    for (int l = captured ? left : 0; l > 0;) {
+        const int m = h->L->steps_per_launch(*h, l);
+        halve ^= m % 2 == 0;
+        l -= m;
+    }
+    for (int half = 0; left > 0;) {
+        int m = half ? half : h->L->steps_per_launch(*h, left);
+        half = 0;
+        if (halve && m % 2 == 0) {
+            half = m /= 2;
+            halve = false;
+        }
         void *const in = h->pop[cur], *const out = h->pop[cur ^ 1];
         const hipError_t e = m > 1 ? h->L->multi(*h, m, in, out, qhist, s) : h->L->step(*h, in, out, qhist, s);
         if (e != hipSuccess) return e;
@@ -797,7 +823,7 @@ static int run_steps(lbm_state *h, int n, void *qhist)
             for (int left = len; left > 0; cur ^= 1) left -= h->L->steps_per_launch(*h, left);
             rc = replay(h, key, [&](hipStream_t s) {
                 int c = cur0, left = len;
-                return enqueue_steps(h, left, q0, stride, c, s);
+                return enqueue_steps(h, left, q0, stride, c, s, false);
             });
             if (rc) return rc;
             h->cur = cur;
@@ -807,7 +833,7 @@ static int run_steps(lbm_state *h, int n, void *qhist)
     if (j < n && h->check_every == 0 && !(h->sys == SYS_NSF17 && h->mms_on)) {
         int left = n - j;
         const hipError_t e = enqueue_steps(h, left, qhist ? (char *)qhist + (size_t)j * stride : nullptr, stride, h->cur,
-                                           h->stream);
+                                           h->stream, n > 1 && capturing(h));
         h->nsteps += n - j - left;
         return e == hipSuccess ? LBM_OK : hipfail(h, e, "step");
     }
