@@ -136,10 +136,12 @@ __host__ __device__ inline Dual<R, N> lbm_sqrt(const Dual<R, N> &a)
 // double (an expression of Wd and double values is plain double arithmetic).
 // Their quotients, roots and logarithms need relative errors far below the
 // 2^-24 of the store they end in, not correct rounding: lbm_div, lbm_sqrt_of
-// and lbm_log1p_of take the parameter type R and use, for Wd, a reciprocal
-// from the float instruction and one Newton step (relative error below
-// 2^-43; 6 instructions against about 16 of the IEEE division), and series of
-// that accuracy.
+// and lbm_log1p_of take the parameter type R and use, for Wd, the double
+// instruction's estimate (about 2^-24) and one Newton step, and series of that
+// accuracy: five instructions against about 16 of the IEEE division.  The float
+// instruction's estimate costs the same with its two conversions, but has the
+// float range: its results beyond 2^126 and those of products below 2^-126 are
+// lost (a relativistic fluid of energy 2^-66: not a number).
 struct Wd {
     double v;
     Wd() = default;
@@ -147,12 +149,13 @@ struct Wd {
     __host__ __device__ constexpr operator double() const { return v; }
 };
 
-// 1 / x of a double within the float range
+// 1 / x.  Where the estimate is infinite or zero its error is not a number,
+// and the minimum takes the other operand: 1 / 0 and 1 / inf are inf and 0.
 __host__ __device__ inline double lbm_rcp_wide(double x)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    const double r = (double)__builtin_amdgcn_rcpf((float)x);
-    return fma(r, fma(-x, r, 1.0), r);
+    const double r = __builtin_amdgcn_rcp(x);
+    return fma(r, fmin(fma(-x, r, 1.0), 0.5), r);
 #else
     return 1.0 / x;
 #endif
@@ -172,9 +175,10 @@ __host__ __device__ inline S lbm_sqrt_of(const S &x)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     if constexpr (std::is_same<R, Wd>::value) {
-        // y = x rsqrt(x), one Newton step from the float reciprocal root
-        const double r = (double)__builtin_amdgcn_rsqf((float)x), y = x * r;
-        return fma(fma(-y, y, x), 0.5 * r, y);
+        // y = x rsqrt(x) and one Newton step; zeros and infinity (class bits)
+        // are their own roots
+        const double r = __builtin_amdgcn_rsq(x), y = x * r;
+        return __builtin_amdgcn_class(x, 0x260) ? x : fma(fma(-y, y, x), 0.5 * r, y);
     } else
 #endif
         return lbm_sqrt(x);
