@@ -624,15 +624,13 @@ struct ImplNE {
             o32 ? launch<false, true>(h, fin, fout, p, s) : launch<false, false>(h, fin, fout, p, s);
         return hipGetLastError();
     }
-    // Several steps per launch on grids that fill the chip (see k_march_ne):
-    // from 2000 strip rows on, as for the other storages; below, the halo costs
-    // more than the launches.
+    // several steps per launch (k_march_ne) where that pays (march_plan.hpp)
     static constexpr int kMost = ne_march_most<Sys, Lat>();
-    static int steps_per_launch(const lbm_state_impl &h, int want)
+    static int steps_per_launch(const lbm_state_impl &h, int want, bool)
     {
-        if (kMost < 2 || want < 2 || !march_fits(h.nx, h.ny, Sys::K * Lat::Q, 2)) return 1;
-        if ((long long)((h.nx + 61) / 62) * h.ny < 2000) return 1;
-        return want >= kMost && !(kMost == 3 && want == 4) ? kMost : 2;
+        const StepState s = {3, Sys::K, Lat::Q, false, h.field_b != nullptr, false};
+        return march_steps(s, kMost, ne_march_lds<Sys, Lat>(kMost), ne_march_lds<Sys, Lat>(2), [](int T) { return T; }, want,
+                           h.nx, h.ny);
     }
     template <int T>
     static hipError_t launch_march(const lbm_state_impl &h, const void *fin, void *fout, hipStream_t s)

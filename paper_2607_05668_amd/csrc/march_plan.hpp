@@ -1,5 +1,6 @@
 // Host arithmetic of the marching kernels' launches (march.hpp): strips,
-// segments and the limits of a lane's addresses.  Plain C++.
+// segments, the limits of a lane's addresses, and where a march pays.  Plain
+// C++.
 #pragma once
 
 #include <algorithm>
@@ -42,4 +43,82 @@ inline int march_rows(int halo, int lds, int populations, int nx, int ny)
     const int r1 = rows_for(kSimds), r2 = rows_for(two);
     const double c1 = r1 + halo, c2 = (populations <= 30 ? 1.75 : 1.5) * (r2 + halo);
     return c1 <= c2 || two <= kSimds ? r1 : r2;
+}
+
+// ------------------------------------------------- where a march pays ----
+// A march moves a state through memory once for its steps, and pays with lanes
+// and rows that are computed and not stored: all of it where the grid is a few
+// columns wide, much of it where the segments are a few rows long.  Its time
+// against that of the single step decides.  Both are fitted to 60 grids from
+// 64^2 to 2048^2, 1 x 200000 and 300000 x 5 in 47 states (2035 pairs; the march
+// to 13%, the single step mostly to 15%).  Against the single step, two launches
+// of a hundred end up slower, by at most 19%, on grids a few rows high; by a
+// rule on rows alone a march was up to 22 times slower (200000 rows of one
+// cell) and 1.2-1.4 times for binary16 at 512^2.  us per step, one step a
+// launch / march: shallow water D2Q9 float 512^2 9.6 / 7.0, 200000 x 1
+// 8.9 / 120; binary16 512^2 6.3 / 8.4, 2048^2 77.8 / 50.1.
+struct StepState {
+    int storage;                    // 0 double, 1 float, 2 binary16, 3 binary16 deviations
+    int fields, velocities;
+    bool two_rates;                 // two-relaxation-time collision
+    bool sources;                   // coefficient or source fields are read
+    bool record;                    // every step's moments are stored
+};
+// us: a launch, a population's row (loads and stores) and stage of a wavefront
+// that has its SIMD to itself, and the least time of a single step per population
+struct StepCosts { double launch, row, stage, least; };
+constexpr StepCosts kStepCosts[4] = {{2.0, 0.073, 0.054, 0.14}, {2.5, 0.042, 0.0146, 0.055}, {3.0, 0.024, 0.0282, 0.07},
+                                     {2.3, 0.027, 0.029, 0.11}};
+constexpr int kStepBytes[4] = {8, 4, 2, 2};
+
+// bytes of both buffers through the last-level cache where they fit, or HBM
+inline double memory_us(double bytes) { return bytes / (bytes < 268e6 ? 6.9e6 : 6.0e6); }
+
+inline double state_bytes(const StepState &s, int nx, int ny)
+{
+    const double moments = s.storage == 3 ? 8.0 * s.fields : 0.0;
+    return (2.0 * s.fields * s.velocities * kStepBytes[s.storage] + moments) * nx * ny;
+}
+
+inline double single_step_us(const StepState &s, int nx, int ny)
+{
+    const int n = s.fields * s.velocities;
+    const double bytes = state_bytes(s, nx, ny), least = 2.0 + kStepCosts[s.storage].least * n;
+    if (s.storage == 3) {           // tiles of 64 x 4 cells, partly empty on narrow grids
+        const double tiles = (double)((nx - 1) / 64 + 1) * ((ny - 1) / 4 + 1);
+        return 1.12 * std::max(least, 2.0 + std::max(bytes / (bytes < 268e6 ? 5.0e6 : 4.5e6), 256 * tiles * n * 0.65e-6));
+    }
+    return std::max(least, 1.7 + memory_us(bytes) + 0.35 * (least - 1.7));
+}
+
+// per step, of a march of T steps that loses `halo` rows and lanes at each end
+inline double march_us(const StepState &s, int T, int halo, int lds, int nx, int ny)
+{
+    const int n = s.fields * s.velocities, rows = march_rows(halo, lds, n, nx, ny);
+    const int two = std::min(2 * kSimds, kSimds / 4 * (kLdsPerCu / lds));
+    const long long waves = (long long)march_strips(halo, nx) * march_segments(ny, rows);
+    // a second wavefront on the SIMDs, and rounds of wavefronts beyond that
+    const double share = (waves <= kSimds + kSimds / 20 ? 1.0 : 1.4) * (double)((waves - 1) / two + 1);
+    const StepCosts &c = kStepCosts[s.storage];
+    double work = n * (c.row * (rows + 2 * halo) + c.stage * T * (rows + halo));
+    work *= s.two_rates ? 1.25 : (s.sources ? 1.1 : 1.0);
+    if (s.record) work += 0.11 * s.fields * T * (rows + 2 * halo);
+    return (c.launch + std::max(share * work, memory_us(state_bytes(s, nx, ny)))) / T;
+}
+
+// Steps of the next launch when `want` are left: `most` (LDS lds_most) or two
+// (LDS lds_two) in a march, or one.  Strips less than half full never pay
+// against the 64-cell tiles of the single step by much.  Three steps as two and
+// one have to gain more: the single step finds what the march left in the L2 of
+// other XCDs (shallow water D2Q9 double 512^2, three steps: 67 us in place of 56
+// for the two kernels by themselves).  halo(T): rows lost.
+template <class Halo>
+int march_steps(const StepState &s, int most, int lds_most, int lds_two, Halo &&halo, int want, int nx, int ny)
+{
+    if (want < 2 || most < 2 || nx < 32 || !march_fits(nx, ny, s.fields * s.velocities, kStepBytes[s.storage])) return 1;
+    const double single = 0.97 * single_step_us(s, nx, ny);
+    if (most > 2 && want >= most && !(most == 3 && want == 4) && march_us(s, most, halo(most), lds_most, nx, ny) <= single)
+        return most;
+    const double gain = want == 3 ? 0.7 : (most > 2 ? 0.9 : 1.0);
+    return march_us(s, 2, halo(2), lds_two, nx, ny) <= gain * single ? 2 : 1;
 }

@@ -708,6 +708,9 @@ struct Impl {
     // 8.66; Euler 300^2 3.79 / 2.71 / 2.73 / 3.29; advection-diffusion in double
     // 192^2 3.76 / 2.41 / 2.95 / 3.57, 384^2 7.55 / 5.75 / 6.89 / 8.76;
     // neo-Hookean 200^2 4.95 / 4.59 / 4.10 / 5.19, 256^2 5.71 / 5.29 / 5.83 / 6.42.
+    // The largest binary16 states gain nothing from two squares a CU on, where
+    // the single step moves half the bytes (neo-Hookean D2Q9 binary16 320^2: 7.13
+    // with three steps, 6.48 with one; 40 x 2048 7.42 and 6.28).
     static int square_steps(const lbm_state_impl &h)
     {
         if constexpr (squares<Sys, Lat, St>()) {
@@ -717,7 +720,7 @@ struct Impl {
             for (int steps = 3; steps <= kSquareMost; ++steps) {
                 const long long out = square_out(steps);
                 const double n = (double)((h.nx + out - 1) / out) * (double)((h.ny + out - 1) / out);
-                if (steps == 3 && n > 4 * cus) return 0;
+                if (steps == 3 && n > (sizeof(St) == 2 && Sys::K * Lat::Q > 50 ? 2 : 4) * cus) return 0;
                 const double cost = 3.0 / steps + 0.55 * std::max(0.0, n / cus - 1);
                 if (!best || cost < least) best = steps, least = cost;
             }
@@ -725,22 +728,19 @@ struct Impl {
         }
         return 0;
     }
-    // Steps of the next launch when `want` are left (1: k_step).  Small grids
-    // take k_square.  Else a grid of at most 700 strip rows (wavefronts of one
-    // row each) takes two steps a launch: the launch costs as much as the
-    // arithmetic of a row, and SIMDs are free for the halo (shallow water 64^2:
-    // 2.93 -> 2.60 us per step, 150 x 101: 3.11 -> 2.86).  Up to 2000 strip rows the chip has no room for
-    // the halo (256^2: one step 3.77, two 4.10, three 4.02 us); beyond, fewer
-    // passes over memory pay (384^2: 6.0 -> 5.3, 512^2: 9.3 -> 7.0).
-    static int steps_per_launch(const lbm_state_impl &h, int want)
+    // Steps of the next launch when `want` are left (1: k_step): squares on small
+    // grids, else a march where it pays (march_plan.hpp).
+    static int steps_per_launch(const lbm_state_impl &h, int want, bool record)
     {
-        if (!kMarch || want < 2 || h.regularized) return 1;
-        if (const int most = square_steps(h)) return std::min(most, want);
-        if (!march_fits(h.nx, h.ny, Sys::K * Lat::Q, sizeof(St))) return 1;
-        const long long strip_rows = (long long)((h.nx + 61) / 62) * h.ny;
-        if (strip_rows <= 700) return 2;
-        if (strip_rows < 2000) return 1;
-        return want >= kMost && !(kMost == 3 && want == 4) ? kMost : 2;
+        if constexpr (kMarch) {
+            if (want < 2 || h.regularized) return 1;
+            if (const int most = square_steps(h)) return std::min(most, want);
+            constexpr int storage = std::is_same<St, double>::value ? 0 : (std::is_same<St, float>::value ? 1 : 2);
+            const StepState s = {storage, Sys::K, Lat::Q, h.trt_lambda > 0, h.field_b || h.field_src, record};
+            return march_steps(s, kMost, march_lds<Sys, Lat, St>(kMost), march_lds<Sys, Lat, St>(2), [](int T) { return T - 1; },
+                               want, h.nx, h.ny);
+        }
+        return 1;
     }
     template <int T, bool EXT, bool REC, int COLL>
     static void launch_march(const lbm_state_impl &h, const void *fin, void *fout, void *qhist, hipStream_t s)

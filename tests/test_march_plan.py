@@ -69,3 +69,41 @@ def test_segments_cover_every_row_once(tmp_path):
                     }
     puts("ok");""")
     assert out == "ok\n"
+
+
+# us per step on an MI355X: storage code, fields, velocities, steps of a march,
+# rows, columns, one step a launch, the march
+MEASURED = [
+    (1, 3, 9, 4, 512, 512, 9.61, 6.95), (1, 3, 9, 4, 1024, 1024, 32.57, 15.61), (1, 3, 9, 4, 2048, 2048, 149.3, 58.08),
+    (1, 3, 9, 4, 200000, 1, 8.94, 120.5), (1, 3, 9, 4, 43400, 3, 5.77, 29.03), (1, 3, 9, 4, 300000, 5, 55.21, 178.8),
+    (1, 3, 9, 4, 20000, 65, 48.34, 28.23), (1, 3, 9, 4, 20, 40000, 26.03, 14.40), (1, 4, 5, 4, 1500, 1500, 60.05, 24.38),
+    (2, 3, 9, 4, 512, 512, 6.32, 8.42), (2, 3, 9, 4, 640, 640, 9.11, 10.98), (2, 3, 9, 4, 1024, 1024, 18.07, 20.74),
+    (2, 3, 9, 4, 2048, 2048, 77.75, 50.07), (2, 3, 9, 4, 200000, 1, 5.96, 119.3), (2, 3, 9, 4, 20000, 65, 21.33, 28.66),
+    (2, 6, 9, 4, 300, 700, 10.69, 14.08), (2, 6, 9, 4, 2048, 2048, 150.9, 100.2), (0, 4, 5, 3, 800, 800, 30.52, 21.11),
+    (0, 4, 5, 3, 1500, 1500, 129.0, 66.90), (0, 4, 5, 3, 200000, 1, 13.11, 252.0), (0, 4, 5, 3, 43400, 3, 8.98, 59.17),
+    (3, 3, 9, 4, 2048, 2048, 110.8, 68.55), (3, 6, 9, 2, 2048, 2048, 224.3, 153.2), (3, 12, 5, 2, 2048, 40, 12.50, 16.45),
+]
+
+
+def test_marches_are_taken_where_they_were_measured_faster(tmp_path):
+    rows = []
+    for st, k, q, t, ny, nx, single, march in MEASURED:
+        slots, e = (9 if q == 9 else 5), {0: 8, 1: 4, 2: 2, 3: 4}[st]
+        lds = [((n if st == 3 else n - 1) * slots * k * 64 + 2) * e for n in (t, 2)]
+        rows.append(f"{{{st}, {k}, {q}, {t}, {lds[0]}, {lds[1]}, {ny}, {nx}, {int(march < single)}}}")
+    out = run(tmp_path, "const int m[][9] = {" + ", ".join(rows) + "};" + r"""
+    int wrong = 0;
+    for (auto &r : m) {
+        const StepState s = {r[0], r[1], r[2], false, false, false};
+        auto halo = [&](int T) { return r[0] == 3 ? T : T - 1; };
+        const int n = march_steps(s, r[3], r[4], r[5], halo, 40, r[7], r[6]);
+        if ((n > 1) != (r[8] != 0) || (n > 1 && n != r[3] && n != 2)) {
+            printf("storage %d, %d fields, %d x %d: %d steps a launch\n", r[0], r[1], r[6], r[7], n);
+            ++wrong;
+        }
+        // one step left, and what the kernels do not hold
+        if (march_steps(s, r[3], r[4], r[5], halo, 1, r[7], r[6]) != 1) ++wrong;
+        if (march_steps(s, r[3], r[4], r[5], halo, 40, 0x7fffffff / 8, 4) != 1) ++wrong;
+    }
+    printf("%d\n", wrong);""")
+    assert out == "0\n", out
