@@ -213,175 +213,6 @@ struct Cell {
     __device__ __forceinline__ static void plain(const KParams<F> &p, const F (*f)[Q], Ext &ex,
                                                  const F *Smms, F *dQ, Emit &emit)
     {
-        using R = F;
-        // moments (eq. moments) by compensated summation: dQ = hi + lo exactly
-        // up to the rounding of lo (two-sum of each addition).  Binary16 storage
-        // sums plainly: each stored population already carries a rounding of
-        // 2^-12 of its magnitude, where the FP32 sum adds ~Q 2^-24, and the
-        // two-sums would be a fifth of the step's instructions.
-        constexpr bool COMP = Sys::compensated && !F16;
-        R dQlo[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            R s = f[k][0], c = R(0);
-#pragma unroll
-            for (int i = 1; i < Q; ++i) {
-                const R t = s + f[k][i];
-                if constexpr (COMP) {
-                    const R bp = t - s;
-                    c += (s - (t - bp)) + (f[k][i] - bp);
-                }
-                s = t;
-            }
-            dQ[k] = F16 ? s * (R)p.inv_scale[k] : s;
-            dQlo[k] = c;
-        }
-        // Double-precision steppers of the precise systems evaluate the flux
-        // deviation at the compensated moments: dPhi(hi) and, from one
-        // forward-mode tangent, its first-order correction J(hi) lo.
-        constexpr bool PRECISE = Sys::precise && !F16;
-        R bl[NB], dPhi[K][D], dPhiLo[K][D];
-        coefficients(p, ex, bl);
-        static_assert(!(PRECISE && CT::in_flux), "coefficient-dependent fluxes use the plain equilibrium");
-        if constexpr (CT::in_flux) {
-            Sys::template flux_delta_b<R, R>(p.phys, dQ, bl, dPhi);
-        } else if constexpr (PRECISE) {
-            using D1 = Dual<R, 1>;
-            D1 q1[K], P1[K][D];
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                q1[k] = D1(dQ[k]);
-                q1[k].d[0] = dQlo[k];
-            }
-            Sys::template flux_delta<D1, R>(p.phys, q1, P1);
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-#pragma unroll
-                for (int a = 0; a < D; ++a) {
-                    dPhi[k][a] = P1[k][a].v;
-                    dPhiLo[k][a] = P1[k][a].d[0];
-                }
-        } else {
-            Sys::template flux_delta<R, R>(p.phys, dQ, dPhi);
-        }
-        // Float-float equilibria e = e_hi + e_lo from the flux deviation and its
-        // first-order correction J(hi) lo.
-        constexpr bool FFEQ = PRECISE;
-        R Sk[K];
-        Sys::template source<R, R>(p.phys, dQ, bl, Sk);
-        if (Ext::ext && p.sext) {
-            // explicit per-cell source (e.g. a manufactured-solution forcing
-            // evaluated at t + dt/2 by the caller)
-#pragma unroll
-            for (int k = 0; k < K; ++k) Sk[k] += ex.s(k);
-        }
-        if constexpr (Sys::id == SYS_NSF17) {
-#pragma unroll
-            for (int k = 0; k < 5; ++k) Sk[k] += Smms[k];
-        }
-        // BGK relaxation post = omega feq + (1 - omega) f written as
-        // post = e + c1 (e - f) with c1 = omega - 1 exactly representable (the
-        // host places 2 - omega on the 2^-24 grid): e - f is exact when f is
-        // within a factor two of e, so the update rounds once.  In the precise
-        // path e = e_hi + e_lo and post = e_hi + (c1 (e_hi - f) + omega e_lo).
-        // Two-relaxation-time (TRT): with d_i = e_i - f_i and ib the opposite
-        // velocity, relaxing the symmetric and antisymmetric parts at omega+ and
-        // omega- is post_i = f_i + a d_i + b d_ib, a = (omega+ + omega-)/2 (in c1
-        // = a - 1 and c2 = a), b = (omega+ - omega-)/2: the BGK update plus
-        // b d_ib.  Regularized: post_i = e_i + (1 - omega) w_i c_i . Pi1 / cs^2
-        // with Pi1 = sum_i c_i (f_i - e_i), the non-equilibrium part projected
-        // on the first-order Hermite polynomial.
-        // The rest population closes the zeroth moment,
-        // post_0 = f_0 + dt S + sum_{i>0} (f_i - post_i), an identity of the
-        // update (the weights sum to one, the flux enters only odd moments)
-        // evaluated with the stored values of post_i, so each cell's
-        // post-collision moment carries a single storage rounding.
-        // Binary16: the field's power-of-two storage scale multiplies the
-        // moment, the flux and the source instead of every population (exact
-        // either way, so the stored values are the same).
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const R c1 = p.c1[k], c2 = p.c2[k];
-            const R sc = F16 ? (R)p.scale[k] : R(1);
-            R s[Q], eh[Q], el[Q];
-            if constexpr (FFEQ) {
-                R Gh[D], Gl[D];
-                FF<R> e[Q];
-#pragma unroll
-                for (int a = 0; a < D; ++a) {
-                    Gh[a] = p.lam * dPhi[k][a];
-                    Gl[a] = fma(p.lam, dPhi[k][a], -Gh[a]) + p.lam * dPhiLo[k][a];
-                }
-                ExactEqFF<Lat>::feq(dQ[k], dQlo[k], Gh, Gl, e);
-#pragma unroll
-                for (int i = 1; i < Q; ++i) {
-                    eh[i] = e[i].hi;
-                    el[i] = e[i].lo;
-                }
-            } else {
-                R G[D];
-#pragma unroll
-                for (int a = 0; a < D; ++a) G[a] = F16 ? sc * (p.lam * dPhi[k][a]) : p.lam * dPhi[k][a];
-                ExactEq<Lat>::feq(F16 ? sc * dQ[k] : dQ[k], dQlo[k], G, eh);
-            }
-            const R dts = F16 ? sc * (p.dt * Sk[k]) : p.dt * Sk[k];
-            ExactEq<Lat>::zeroth(dts, s);
-            R acc = dts;
-            constexpr bool TRT = COLL == COLL_TRT;
-            R bd[Q];                         // TRT: b d_i
-            R P1[D];                         // regularized: sum_i c_i (f_i - e_i)
-            if constexpr (COLL == COLL_REG) {
-#pragma unroll
-                for (int a = 0; a < D; ++a) P1[a] = R(0);
-#pragma unroll
-                for (int i = 1; i < Q; ++i) {
-                    R d = f[k][i] - eh[i];
-                    if constexpr (FFEQ) d = d - el[i];
-#pragma unroll
-                    for (int a = 0; a < D; ++a)
-                        if (lat_c<Lat>(i, a) != 0) P1[a] = lat_c<Lat>(i, a) > 0 ? P1[a] + d : P1[a] - d;
-                }
-            }
-            if constexpr (TRT) {
-                const R tb = p.tb[k];
-#pragma unroll
-                for (int i = 1; i < Q; ++i) {
-                    if constexpr (FFEQ)
-                        bd[i] = tb * ((eh[i] - f[k][i]) + el[i]);
-                    else
-                        bd[i] = tb * (eh[i] - f[k][i]);
-                }
-            }
-#pragma unroll
-            for (int i = 1; i < Q; ++i) {
-                const R fi = f[k][i];
-                R post;
-                if constexpr (COLL == COLL_REG) {
-                    R cp = R(0);
-#pragma unroll
-                    for (int a = 0; a < D; ++a)
-                        if (lat_c<Lat>(i, a) != 0) cp = lat_c<Lat>(i, a) > 0 ? cp + P1[a] : cp - P1[a];
-                    // (1 - omega) w_i / cs^2 (c_i . Pi1), with w_i / cs^2 = Wn_i / Fden
-                    const R rg = (-c1) * (cp * (R(Lat::Wn[i]) / R(Lat::Fden)));
-                    if constexpr (FFEQ)
-                        post = eh[i] + ((el[i] + rg) + s[i]);
-                    else
-                        post = eh[i] + (rg + s[i]);
-                } else if constexpr (TRT) {
-                    if constexpr (FFEQ)
-                        post = eh[i] + (fma(c1, eh[i] - fi, fma(c2, el[i], bd[Lat::opp[i]])) + s[i]);
-                    else
-                        post = fma(c1, eh[i] - fi, eh[i] + bd[Lat::opp[i]]) + s[i];
-                } else if constexpr (FFEQ) {
-                    post = eh[i] + (fma(c1, eh[i] - fi, c2 * el[i]) + s[i]);
-                } else {
-                    post = fma(c1, eh[i] - fi, eh[i]) + s[i];
-                }
-                const St st = (St)post;
-                emit(k, i, st);
-                acc += fi - (R)st;
-            }
-            emit(k, 0, (St)(f[k][0] + acc));
-        }
+#include "collide_plain.inc"
     }
 };

@@ -230,11 +230,21 @@ __global__ __launch_bounds__((step_block<Sys, St>())) void k_step(const St *__re
 #pragma unroll
         for (int i = 0; i < Q; ++i)
             f[k][i] = Store<St>::ld(byte_at(fin + (size_t)zs[i] * slab + (size_t)(k * Q + i) * kTile, src[i]));
-    const CellFields<R, I> ex = {(const R *)p.b, (const R *)p.sext, (size_t)p.C, cell * (I)sizeof(R)};
+    using F = R;
+    using CT = typename C::CT;
+    using Ext = CellFields<R, I>;
+    constexpr bool F16 = C::F16;
+    constexpr int NB = C::NB;
+    const Ext ex = {(const R *)p.b, (const R *)p.sext, (size_t)p.C, cell * (I)sizeof(R)};
     R dQ[K];
-    C::update(p, f, ex, Smms, dQ, [&](int k, int i, St v) {
+    auto emit = [&](int k, int i, St v) {
         st_pop<NT>(byte_at(fout + (size_t)z * slab + (size_t)(k * Q + i) * kTile, own), v);
-    });
+    };
+    if constexpr (C::WIDE || C::WIDEQ) {
+        C::update(p, f, ex, Smms, dQ, emit);
+    } else {
+#include "collide_plain.inc"
+    }
     if constexpr (REC) {
 #pragma unroll
         for (int k = 0; k < K; ++k) *byte_at(qhist + k * (size_t)p.C, cell * (I)sizeof(R)) = dQ[k];
