@@ -10,7 +10,8 @@ import pytest
 
 from paper_2607_05668_amd import lbm
 
-READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+LLVM = "/opt/rocm/llvm/bin/"
+READELF = LLVM + "llvm-readelf"
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 pytestmark = pytest.mark.skipif(shutil.which(READELF) is None, reason="no llvm-readelf")
 
@@ -35,7 +36,7 @@ def kernels(tmp_path_factory):
                 get = lambda key: re.search(rf"\.{key}: +(\S+)", k).group(1)      # noqa: E731
                 out[get("name")] = (int(get("vgpr_count")), int(get("private_segment_fixed_size")))
         at = data.find(MAGIC, at + 1)
-    names = subprocess.run(["c++filt"], input="\n".join(out), capture_output=True, text=True, check=True).stdout.split("\n")
+    names = subprocess.run([LLVM + "llvm-cxxfilt"], input="\n".join(out), capture_output=True, text=True, check=True).stdout.split("\n")
     return dict(zip(names, out.values()))
 
 
