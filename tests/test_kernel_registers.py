@@ -10,15 +10,14 @@ import pytest
 
 from paper_2607_05668_amd import lbm
 
-LLVM = "/opt/rocm/llvm/bin/"
-READELF = LLVM + "llvm-readelf"
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
 MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 pytestmark = pytest.mark.skipif(shutil.which(READELF) is None, reason="no llvm-readelf")
 
 
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
-    """Demangled kernel name -> (registers a lane, bytes of scratch a lane)."""
+    """Kernel symbol -> (registers a lane, bytes of scratch a lane)."""
     data = open(lbm.LIB_PATH, "rb").read()
     folder = tmp_path_factory.mktemp("objects")
     out, at = {}, data.find(MAGIC)
@@ -36,32 +35,37 @@ def kernels(tmp_path_factory):
                 get = lambda key: re.search(rf"\.{key}: +(\S+)", k).group(1)      # noqa: E731
                 out[get("name")] = (int(get("vgpr_count")), int(get("private_segment_fixed_size")))
         at = data.find(MAGIC, at + 1)
-    names = subprocess.run([LLVM + "llvm-cxxfilt"], input="\n".join(out), capture_output=True, text=True, check=True).stdout.split("\n")
-    return dict(zip(names, out.values()))
+    return out
 
 
-def _matching(kernels, pattern):
-    found = {k: v for k, v in kernels.items() if re.search(pattern, k)}
-    assert found, pattern
+def _matching(kernels, kernel, system, lattice, rest):
+    """Instantiations kernel<system, lattice, rest...> (mangled, a regular expression)."""
+    start = f"{len(kernel)}{kernel}I{len(system)}{system}{len(lattice)}{lattice}{rest}"
+    found = {k: v for k, v in kernels.items() if re.match("_Z" + start, k)}
+    assert found, start
     return found
 
 
+def _single_steps_in_double(kernels, system, lattice):      # no history, 32-bit offsets, BGK
+    return _matching(kernels, "k_step", system, lattice, "dLb0ELb[01]ELb1ELi0EE").items()
+
+
 # two wavefronts a SIMD hold 256 registers each
-@pytest.mark.parametrize("state", ["SysCNSF2D, D2Q5, double", "SysNeoHooke, D2Q9, double"])
+@pytest.mark.parametrize("state", [("SysCNSF2D", "D2Q5"), ("SysNeoHooke", "D2Q9")])
 def test_single_steps_in_double_leave_two_wavefronts_a_simd(kernels, state):
-    for name, (registers, _) in _matching(kernels, rf"k_step<{state}, false, \w+, true, 0>").items():
+    for name, (registers, _) in _single_steps_in_double(kernels, *state):
         assert registers <= 256, (name, registers)
 
 
 # states that fill one wavefront's 512 registers
-@pytest.mark.parametrize("state,scratch", [("SysCNSF2D, D2Q9, double", 0), ("SysMHD, D2Q9, double", 900),
-                                           ("SysNSF17, D3Q7, double", 64)])
+@pytest.mark.parametrize("state,scratch", [(("SysCNSF2D", "D2Q9"), 0), (("SysMHD", "D2Q9"), 900),
+                                           (("SysNSF17", "D3Q7"), 64)])
 def test_single_steps_of_the_largest_states_spill_no_more(kernels, state, scratch):
-    for name, (_, spilled) in _matching(kernels, rf"k_step<{state}, false, \w+, true, 0>").items():
+    for name, (_, spilled) in _single_steps_in_double(kernels, *state):
         assert spilled <= scratch, (name, spilled)
 
 
 # four wavefronts a SIMD hold 128 registers each
 def test_single_step_of_the_deviations_leaves_four_wavefronts_a_simd(kernels):
-    for name, (registers, scratch) in _matching(kernels, r"k_step_ne<SysNeoHooke, D2Q9, ").items():
+    for name, (registers, scratch) in _matching(kernels, "k_step_ne", "SysNeoHooke", "D2Q9", "").items():
         assert registers <= 128 and scratch <= 32, (name, registers, scratch)
