@@ -470,9 +470,13 @@ static __global__ __launch_bounds__(kBlock) void k_reduce2(const double *__restr
 
 // Workgroups of the first pass: enough wavefronts for eight a SIMD, no more
 // than the cells need, and nslot partial results of each within the scratch.
-inline unsigned reduce_blocks(long long C, int nslot)
+// States of more than seven fields hold one to four wavefronts a SIMD: more
+// would wait for a place (largest wave speed of MHD binary16, 1000 x 1100: 93.6
+// us with 2048 workgroups, 81.8 with 1024; 2D NSF D2Q9 double 241 and 225).
+inline unsigned reduce_blocks(long long C, int nslot, int fields)
 {
-    const long long most = std::min<long long>(2 * kRedBlocks, (long long)2 * LBM_MAXK * kRedBlocks / nslot);
+    const long long full = fields > 7 ? kRedBlocks : 2 * kRedBlocks;
+    const long long most = std::min<long long>(full, (long long)2 * LBM_MAXK * kRedBlocks / nslot);
     return (unsigned)std::max<long long>(1, std::min(most, (C + kBlock - 1) / kBlock));
 }
 
@@ -529,7 +533,10 @@ __global__ __launch_bounds__(kBlock) void k_adj_step(const R *__restrict__ lin, 
 #pragma unroll
         for (int a = 0; a < 2; ++a) gb[a] = *byte_at(grad_b + (size_t)a * C, own);
     }
-    __builtin_amdgcn_sched_barrier(0);
+    // Shallow water issues all loads first.  Jacobians of more arithmetic use the
+    // moments before that (compiled Euler D2Q5 float 1000 x 1100: 42.9 us behind
+    // the barrier, 38.2 without).
+    if constexpr (Sys::id == SYS_SWE) __builtin_amdgcn_sched_barrier(0);
     DK dPhi[K][D], Sk[K];
     Sys::template flux_delta<DK, R>(p.phys, dQ, dPhi);
     // M0_k = sum_i w_i mu_{k,i} and L1_{k,a} = (lam/cs2) sum_i w_i c_ia mu_{k,i},
@@ -870,7 +877,7 @@ struct Impl {
         const KParams<double> p = h.kparams<double>(h.t0);
         const int nslot = (what == 3 || what == 4) ? 1 : (what == 0 ? Sys::K : 2 * Sys::K);
         const int is_max = (what == 2 || what == 3) ? 1 : 0;
-        const unsigned nb = reduce_blocks(h.C, nslot);
+        const unsigned nb = reduce_blocks(h.C, nslot, Sys::K);
         auto go = [&](auto kern) {
             hipLaunchKernelGGL(kern, dim3(nb), dim3(kBlock), 0, s, (const St *)fin, ref, aux, p, what);
         };
