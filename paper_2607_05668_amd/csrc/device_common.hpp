@@ -125,10 +125,8 @@ __device__ inline size_t pop_at(int k, int i, long long c, long long P)
 // grid has fewer than 2^32 cells (their divisions by the extents are most of
 // the arithmetic of a kernel that only sums populations).
 template <int K, class Lat, class I>
-__device__ inline void pulled_places(I cell, int nx, int ny, int nz, size_t *at)
+__device__ inline void pulled_places_of(int x, int y, int z, int nx, int ny, int nz, size_t *at)
 {
-    int x, y, z;
-    cell_coords<I>(cell, nx, ny, x, y, z);
     const I P = (I)nx * (I)ny;
     const size_t slab = (size_t)K * Lat::Q * ((P + (I)(kTile - 1)) / (I)kTile) * kTile;
 #pragma unroll
@@ -138,6 +136,13 @@ __device__ inline void pulled_places(I cell, int nx, int ny, int nz, size_t *at)
         at[i] = (size_t)zs * slab + (size_t)(c / (I)kTile) * (size_t)(K * Lat::Q * kTile) + (size_t)(c % (I)kTile)
                 + (size_t)(i * kTile);
     }
+}
+template <int K, class Lat, class I>
+__device__ inline void pulled_places(I cell, int nx, int ny, int nz, size_t *at)
+{
+    int x, y, z;
+    cell_coords<I>(cell, nx, ny, x, y, z);
+    pulled_places_of<K, Lat, I>(x, y, z, nx, ny, nz, at);
 }
 inline bool fits_i32(long long C) { return C < (1ll << 32) - (1ll << 26); }   // also with a grid stride added
 

@@ -351,59 +351,120 @@ __global__ __launch_bounds__(64) void k_march_ne(const _Float16 *__restrict__ gi
     }
 }
 
-// A tile's halo senders for the kernels around the step: their equilibria's
-// parts in LDS (one flux evaluation per sender, as in k_step_ne), moment(k, c)
-// giving a cell's stored moments.  Ends with a barrier.
+// ---- kernels around the step: initialisation, moments, reductions ----
+// A cell's populations are its senders' deviations and equilibria.  TILED: a
+// workgroup takes 64 x 4 cells and forms each sender's equilibrium once, in LDS
+// (as k_step_ne does).  Else it takes 256 consecutive cells and each forms its
+// senders' by itself: three to six times the flux evaluations, but no lane is
+// idle on grids narrower than the tiles and nothing waits for a barrier.
 constexpr int kNeHX = kNeTX + 2, kNeHY = kNeTY + 2, kNeHalo = kNeHX * kNeHY, kNeThreads = kNeTX * kNeTY;
-template <class Sys, class Lat, class Moment>
-__device__ __forceinline__ void ne_senders(const KParams<float> &p, int tx0, int ty0, float (*sP)[3][kNeHalo],
-                                           Moment &&moment)
-{
-    constexpr int K = Sys::K, D = Lat::D;
-    for (int h = (int)threadIdx.x; h < kNeHalo; h += kNeThreads) {
-        const int hy = h / kNeHX, hx = h - hy * kNeHX;
-        const size_t c = (size_t)pmod(ty0 + hy - 1, p.ny) * p.nx + pmod(tx0 + hx - 1, p.nx);
-        float M[K], P[K][D];
+template <class Sys, bool TILED> constexpr int ne_parts() { return TILED ? Sys::K * 3 * kNeHalo : 1; }
+
+template <class Sys, class Lat, bool TILED>
+struct NeCells {
+    static constexpr int K = Sys::K, D = Lat::D;
+    const KParams<float> &p;
+    float *parts;                       // [K][3][kNeHalo]
+    int x, y, lx, ly;
+    size_t cell;
+    bool live;
+
+    // The cells of tile t; moment(k, c): the stored moments of cell c.  Ends with
+    // a barrier (TILED).
+    template <class Moment>
+    __device__ __forceinline__ void enter(unsigned t, Moment &&moment)
+    {
+        if constexpr (TILED) {
+            const unsigned tilesx = (unsigned)(p.nx - 1) / kNeTX + 1;
+            const int tx0 = (int)(t % tilesx) * kNeTX, ty0 = (int)(t / tilesx) * kNeTY;
+            lx = (int)threadIdx.x % kNeTX;
+            ly = (int)threadIdx.x / kNeTX;
+            x = tx0 + lx;
+            y = ty0 + ly;
+            live = x < p.nx && y < p.ny;
+            cell = (size_t)y * p.nx + x;
+            for (int h = (int)threadIdx.x; h < kNeHalo; h += kNeThreads) {
+                const int hy = h / kNeHX, hx = h - hy * kNeHX;
+                const size_t c = (size_t)pmod(ty0 + hy - 1, p.ny) * p.nx + pmod(tx0 + hx - 1, p.nx);
+                float M[K], P[K][D];
 #pragma unroll
-        for (int k = 0; k < K; ++k) M[k] = moment(k, c);
-        Sys::template flux_delta<float, float>(p.phys, M, P);
+                for (int k = 0; k < K; ++k) M[k] = moment(k, c);
+                Sys::template flux_delta<float, float>(p.phys, M, P);
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            float G[D], Pt[3];
+                for (int k = 0; k < K; ++k) {
+                    float G[D], Pt[3];
 #pragma unroll
-            for (int a = 0; a < D; ++a) G[a] = p.lam * P[k][a];
-            ExactEq<Lat>::parts(M[k], G, Pt);
+                    for (int a = 0; a < D; ++a) G[a] = p.lam * P[k][a];
+                    ExactEq<Lat>::parts(M[k], G, Pt);
 #pragma unroll
-            for (int j = 0; j < 3; ++j) sP[k][j][h] = Pt[j];
+                    for (int j = 0; j < 3; ++j) parts[(k * 3 + j) * kNeHalo + h] = Pt[j];
+                }
+            }
+            __syncthreads();
+        } else {
+            cell = (size_t)t * kNeThreads + threadIdx.x;
+            live = cell < (size_t)p.C;
+            // a 64-bit quotient is a long function
+            y = (int)(p.C < 1ll << 32 ? (unsigned)cell / (unsigned)p.nx : cell / (unsigned)p.nx);
+            x = (int)(cell - (size_t)y * p.nx);
         }
     }
-    __syncthreads();
-}
-// e_i of the sender x - c_i, for the cell at (lx, ly) of the tile
-template <class Lat>
-__device__ __forceinline__ float ne_sent(const float (*sP)[kNeHalo], int lx, int ly, int i)
-{
-    const int h = (ly + 1 - Lat::cy[i]) * kNeHX + (lx + 1 - Lat::cx[i]);
-    const float Pt[3] = {sP[0][h], sP[1][h], sP[2][h]};
-    return i == 0 ? ExactEq<Lat>::rest_parts(Pt) : ExactEq<Lat>::dir(Pt, i);
-}
-// The moments of cell (x, y), summed in double from its rebuilt populations.
-template <class Sys, class Lat>
-__device__ __forceinline__ void ne_moments(const _Float16 *__restrict__ g, const KParams<float> &p,
-                                           const float (*sP)[3][kNeHalo], int x, int y, int lx, int ly, double *q)
-{
-    constexpr int K = Sys::K, Q = Lat::Q;
-    size_t src[Q];
-    pulled_places<K, Lat, unsigned long long>((unsigned long long)y * p.nx + x, p.nx, p.ny, 1, src);
+    // e_i of the sender x - c_i, every field
+    template <class Moment>
+    __device__ __forceinline__ void sent(int i, Moment &&moment, float *e) const
+    {
+        if constexpr (TILED) {
+            const int h = (ly + 1 - Lat::cy[i]) * kNeHX + (lx + 1 - Lat::cx[i]);
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        double s = 0.0;
+            for (int k = 0; k < K; ++k) {
+                const float Pt[3] = {parts[k * 3 * kNeHalo + h], parts[(k * 3 + 1) * kNeHalo + h],
+                                     parts[(k * 3 + 2) * kNeHalo + h]};
+                e[k] = i == 0 ? ExactEq<Lat>::rest_parts(Pt) : ExactEq<Lat>::dir(Pt, i);
+            }
+        } else {
+            const size_t c = (size_t)wrapi(y - Lat::cy[i], p.ny) * p.nx + wrapi(x - Lat::cx[i], p.nx);
+            float M[K], P[K][D];
 #pragma unroll
-        for (int i = 0; i < Q; ++i)
-            s += (double)fmaf((float)g[src[i] + (size_t)(k * Q * kTile)], p.inv_scale[k], ne_sent<Lat>(sP[k], lx, ly, i));
-        q[k] = s;
+            for (int k = 0; k < K; ++k) M[k] = moment(k, c);
+            if (i == 0) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) e[k] = ExactEq<Lat>::rest(M[k]);
+                return;
+            }
+            Sys::template flux_delta<float, float>(p.phys, M, P);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                float G[D], all[Lat::Q];
+#pragma unroll
+                for (int a = 0; a < D; ++a) G[a] = p.lam * P[k][a];
+                ExactEq<Lat>::feq(M[k], 0.0f, G, all);
+                e[k] = all[i];
+            }
+        }
     }
-}
+    // before the next tile's enter
+    __device__ __forceinline__ static void leave()
+    {
+        if constexpr (TILED) __syncthreads();
+    }
+    // the cell's moments, summed in double from its rebuilt populations
+    template <class Moment>
+    __device__ __forceinline__ void moments(const _Float16 *__restrict__ g, Moment &&moment, double *q) const
+    {
+        size_t src[Lat::Q];
+        pulled_places_of<K, Lat, unsigned long long>(x, y, 0, p.nx, p.ny, 1, src);
+#pragma unroll
+        for (int k = 0; k < K; ++k) q[k] = 0.0;
+#pragma unroll
+        for (int i = 0; i < Lat::Q; ++i) {
+            float e[K];
+            sent(i, moment, e);
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                q[k] += (double)fmaf((float)g[src[i] + (size_t)(k * Lat::Q * kTile)], p.inv_scale[k], e[k]);
+        }
+    }
+};
 
 // Initial state: M(y) = Q(y) - Q0 rounded to float and, in the pull layout,
 // g_i(y) = f*eq_i(Q(y + c_i)) - e_i(M(y)) with the equilibrium of the
@@ -414,63 +475,64 @@ __device__ __forceinline__ void ne_moments(const _Float16 *__restrict__ g, const
 // speed of the workgroup, from the moments of the values as stored.
 // Neo-Hookean 2048^2: 363 + 524 us with the receivers' equilibria formed by
 // every sender, and 825 us for the speeds read back.
-template <class Sys, class Lat, bool SCALE>
+template <class Sys, class Lat, bool SCALE, bool TILED>
 __global__ __launch_bounds__(kNeThreads) void k_init_ne(const double *__restrict__ Qin, _Float16 *__restrict__ g,
                                                         float *__restrict__ M, double *__restrict__ part,
                                                         const KParams<double> pd, const KParams<float> pf, unsigned tiles)
 {
     constexpr int K = Sys::K, Q = Lat::Q, D = Lat::D;
-    __shared__ float sP[K][3][kNeHalo];
+    __shared__ float parts[ne_parts<Sys, TILED>()];
     __shared__ double sh[kBlock / 64];
     static_assert(kNeThreads == kBlock, "block reductions");
     const size_t C = (size_t)pd.C;
-    const int tilesx = (pd.nx + kNeTX - 1) / kNeTX;
-    const int lx = (int)threadIdx.x % kNeTX, ly = (int)threadIdx.x / kNeTX;
+    NeCells<Sys, Lat, TILED> at = {pf, parts};
+    const auto moment = [&](int k, size_t c) { return (float)(Qin[(size_t)k * C + c] - pd.phys.Q0[k]); };
     double mx[K], fastest = 0.0;
 #pragma unroll
     for (int k = 0; k < K; ++k) mx[k] = 0.0;
     for (unsigned t = blockIdx.x; t < tiles; t += gridDim.x) {
-        const int tx0 = (int)(t % (unsigned)tilesx) * kNeTX, ty0 = (int)(t / (unsigned)tilesx) * kNeTY;
-        ne_senders<Sys, Lat>(pf, tx0, ty0, sP,
-                             [&](int k, size_t c) { return (float)(Qin[(size_t)k * C + c] - pd.phys.Q0[k]); });
-        const int x = tx0 + lx, y = ty0 + ly;
-        if (x < pd.nx && y < pd.ny) {
-            const size_t cell = (size_t)y * pd.nx + x;
+        at.enter(t, moment);
+        if (at.live) {
             double dq[K], P[K][D], q[K];
 #pragma unroll
-            for (int k = 0; k < K; ++k) dq[k] = Qin[(size_t)k * C + cell] - pd.phys.Q0[k];
+            for (int k = 0; k < K; ++k) dq[k] = Qin[(size_t)k * C + at.cell] - pd.phys.Q0[k];
             Sys::template flux_delta<double, double>(pd.phys, dq, P);
             size_t dst[Q];
-            pulled_places<K, Lat, unsigned long long>(cell, pd.nx, pd.ny, 1, dst);
+            pulled_places_of<K, Lat, unsigned long long>(at.x, at.y, 0, pd.nx, pd.ny, 1, dst);
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                double s = 0.0;
+            for (int k = 0; k < K; ++k) q[k] = 0.0;
 #pragma unroll
-                for (int i = 0; i < Q; ++i) {
+            for (int i = 0; i < Q; ++i) {
+                float e[K];
+                at.sent(i, moment, e);
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
                     double cd = 0.0;
 #pragma unroll
                     for (int a = 0; a < D; ++a) cd += lat_c<Lat>(i, a) * P[k][a];
-                    const float ei = ne_sent<Lat>(sP[k], lx, ly, i);
-                    const double gv = Lat::w[i] * (dq[k] + pd.lam_cs2 * cd) - (double)ei;
+                    const double gv = Lat::w[i] * (dq[k] + pd.lam_cs2 * cd) - (double)e[k];
                     if constexpr (SCALE) {
                         mx[k] = fabs(gv) > mx[k] ? fabs(gv) : mx[k];
                     } else {
                         const _Float16 v = (_Float16)(gv * (double)pf.scale[k]);
                         g[dst[i] + (size_t)(k * Q * kTile)] = v;
-                        s += (double)fmaf((float)v, pf.inv_scale[k], ei);
+                        q[k] += (double)fmaf((float)v, pf.inv_scale[k], e[k]);
                     }
                 }
-                q[k] = s + pd.phys.Q0[k];
-                if constexpr (!SCALE) M[(size_t)k * C + cell] = (float)dq[k];
             }
             if constexpr (!SCALE) {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    M[(size_t)k * C + at.cell] = (float)dq[k];
+                    q[k] += pd.phys.Q0[k];
+                }
                 if (part) {
                     const double v = Sys::template max_speed<double>(pd.phys, q);
                     fastest = v > fastest ? v : fastest;
                 }
             }
         }
-        __syncthreads();
+        at.leave();
     }
     if constexpr (SCALE) {
         for (int k = 0; k < K; ++k) {
@@ -483,35 +545,32 @@ __global__ __launch_bounds__(kNeThreads) void k_init_ne(const double *__restrict
     }
 }
 
-template <class Sys, class Lat, class Out>
+template <class Sys, class Lat, class Out, bool TILED>
 __global__ __launch_bounds__(kNeThreads) void k_moments_ne(const _Float16 *__restrict__ g, const float *__restrict__ M,
                                                            Out *__restrict__ out, const KParams<float> p,
                                                            const KParams<double> pd, int absolute)
 {
     constexpr int K = Sys::K;
-    __shared__ float sP[K][3][kNeHalo];
+    __shared__ float parts[ne_parts<Sys, TILED>()];
     const size_t C = (size_t)p.C;
-    const int tilesx = (p.nx + kNeTX - 1) / kNeTX;
-    const unsigned t = (unsigned)xcd_tile(blockIdx.x, gridDim.x);
-    const int tx0 = (int)(t % (unsigned)tilesx) * kNeTX, ty0 = (int)(t / (unsigned)tilesx) * kNeTY;
-    const int lx = (int)threadIdx.x % kNeTX, ly = (int)threadIdx.x / kNeTX, x = tx0 + lx, y = ty0 + ly;
-    ne_senders<Sys, Lat>(p, tx0, ty0, sP, [&](int k, size_t c) { return M[(size_t)k * C + c]; });
-    if (x >= p.nx || y >= p.ny) return;
+    NeCells<Sys, Lat, TILED> at = {p, parts};
+    const auto moment = [&](int k, size_t c) { return M[(size_t)k * C + c]; };
+    at.enter((unsigned)xcd_tile(blockIdx.x, gridDim.x), moment);
+    if (!at.live) return;
     double q[K];
-    ne_moments<Sys, Lat>(g, p, sP, x, y, lx, ly, q);
+    at.moments(g, moment, q);
 #pragma unroll
-    for (int k = 0; k < K; ++k)
-        out[(size_t)k * C + (size_t)y * p.nx + x] = (Out)(absolute ? q[k] + pd.phys.Q0[k] : q[k]);
+    for (int k = 0; k < K; ++k) out[(size_t)k * C + at.cell] = (Out)(absolute ? q[k] + pd.phys.Q0[k] : q[k]);
 }
 
-template <class Sys, class Lat>
+template <class Sys, class Lat, bool TILED>
 __global__ __launch_bounds__(kNeThreads) void k_reduce1_ne(const _Float16 *__restrict__ g, const float *__restrict__ M,
                                                            const double *__restrict__ ref, double *__restrict__ part,
                                                            const KParams<float> p, const KParams<double> pd, int what,
                                                            unsigned tiles)
 {
     constexpr int K = Sys::K, Q = Lat::Q;
-    __shared__ float sP[K][3][kNeHalo];
+    __shared__ float parts[ne_parts<Sys, TILED>()];
     __shared__ double sh[kBlock / 64];
     const size_t C = (size_t)p.C;
     const unsigned nb = gridDim.x;
@@ -535,19 +594,16 @@ __global__ __launch_bounds__(kNeThreads) void k_reduce1_ne(const _Float16 *__res
         if (threadIdx.x == 0) part[blockIdx.x] = r;
         return;
     }
-    const int tilesx = (p.nx + kNeTX - 1) / kNeTX;
-    const int lx = (int)threadIdx.x % kNeTX, ly = (int)threadIdx.x / kNeTX;
+    NeCells<Sys, Lat, TILED> at = {p, parts};
+    const auto moment = [&](int k, size_t c) { return M[(size_t)k * C + c]; };
     double a0[K], a1[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) a0[k] = a1[k] = 0.0;
     for (unsigned t = blockIdx.x; t < tiles; t += nb) {
-        const int tx0 = (int)(t % (unsigned)tilesx) * kNeTX, ty0 = (int)(t / (unsigned)tilesx) * kNeTY;
-        const int x = tx0 + lx, y = ty0 + ly;
-        ne_senders<Sys, Lat>(p, tx0, ty0, sP, [&](int k, size_t c) { return M[(size_t)k * C + c]; });
-        if (x < p.nx && y < p.ny) {
-            const size_t cell = (size_t)y * p.nx + x;
+        at.enter(t, moment);
+        if (at.live) {
             double q[K];
-            ne_moments<Sys, Lat>(g, p, sP, x, y, lx, ly, q);
+            at.moments(g, moment, q);
 #pragma unroll
             for (int k = 0; k < K; ++k) q[k] += pd.phys.Q0[k];
             if (what == 0) {
@@ -556,14 +612,14 @@ __global__ __launch_bounds__(kNeThreads) void k_reduce1_ne(const _Float16 *__res
             } else if (what == 1) {
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
-                    const double r = ref[(size_t)k * C + cell];
+                    const double r = ref[(size_t)k * C + at.cell];
                     a0[k] += (q[k] - r) * (q[k] - r);
                     a1[k] += r * r;
                 }
             } else if (what == 2) {
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
-                    const double r = ref[(size_t)k * C + cell];
+                    const double r = ref[(size_t)k * C + at.cell];
                     const double e = fabs(q[k] - r);
                     a0[k] = e > a0[k] ? e : a0[k];
                     a1[k] = fabs(r) > a1[k] ? fabs(r) : a1[k];
@@ -573,7 +629,7 @@ __global__ __launch_bounds__(kNeThreads) void k_reduce1_ne(const _Float16 *__res
                 a0[0] = sp > a0[0] ? sp : a0[0];
             }
         }
-        __syncthreads();
+        at.leave();
     }
     const int nslot = (what == 3) ? 1 : (what == 0 ? K : 2 * K);
     for (int j = 0; j < nslot; ++j) {
@@ -665,33 +721,66 @@ struct ImplNE {
         hipLaunchKernelGGL(k_reduce2_ne, dim3(nslot), dim3(kBlock), 0, s, part, part + (size_t)2 * LBM_MAXK * kRedBlocks,
                            nslot, (int)nb, is_max);
     }
+    // Tiles of a kernel around the step (TILED), or its runs of 256 cells.  Tiles
+    // pay where they save D2Q9's eight flux evaluations and are at least four
+    // fifths full: below, idle lanes take what they save (cells / tiles, us:
+    // moments of shallow water D2Q9 1500^2 51 / 34, 20000 x 65 32 / 36, 200^2 6.7 /
+    // 8.3; initialisation of neo-Hookean D2Q9 200000 x 1 167 / 1942), and where
+    // every CU has one or the state is large (64^2: 6.0 / 6.6).  D2Q5's four
+    // evaluations are as fast as the barrier and the LDS they would save, except
+    // for the moments of three to six fields (neo-Hookean 700^2 18.2 / 15.2; sums
+    // of the 7-field flow 1000 x 1100 72 / 113).
+    struct Around {
+        bool tiled;
+        unsigned tiles;
+    };
+    static constexpr bool kTiledMoments = Sys::K > 1 && (Lat::Q == 9 || (Sys::K >= 3 && Sys::K <= 6));
+    static constexpr bool kTiled = Sys::K > 1 && Lat::Q == 9;
+    static Around around(const lbm_state_impl &h, bool may)
+    {
+        const long long tiles = (long long)((h.nx - 1) / kNeTX + 1) * ((h.ny - 1) / kNeTY + 1);
+        const long long runs = (h.C + kNeThreads - 1) / kNeThreads;
+        const bool tiled = may && 5 * h.C >= 4 * kNeThreads * tiles && tiles < 1ll << 24 && (tiles >= kSimds / 4 || Sys::K >= 6);
+        return {tiled, (unsigned)(tiled ? tiles : runs)};
+    }
     static hipError_t init(const lbm_state_impl &h, const double *Q, void *fout, double *speed, hipStream_t s)
     {
-        const unsigned nb = std::min(step_grid(h), (unsigned)kInitBlocks);
-        hipLaunchKernelGGL((k_init_ne<Sys, Lat, false>), dim3(nb), dim3(kNeThreads), 0, s, Q, (_Float16 *)fout,
-                           (float *)mp(h, fout), speed, h.kparams<double>(h.t0), h.kparams<float>(h.t0), step_grid(h));
+        const Around a = around(h, kTiled);
+        const unsigned nb = std::min(a.tiles, (unsigned)kInitBlocks);
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(nb), dim3(kNeThreads), 0, s, Q, (_Float16 *)fout, (float *)mp(h, fout), speed,
+                               h.kparams<double>(h.t0), h.kparams<float>(h.t0), a.tiles);
+        };
+        a.tiled ? go(k_init_ne<Sys, Lat, false, kTiled>) : go(k_init_ne<Sys, Lat, false, false>);
         if (speed) combine(speed, 1, nb, 1, s);
         return hipGetLastError();
     }
     static hipError_t init_absmax(const lbm_state_impl &h, const double *Q, double *part, hipStream_t s)
     {
-        const unsigned nb = std::min(step_grid(h), (unsigned)(2 * kRedBlocks));
-        hipLaunchKernelGGL((k_init_ne<Sys, Lat, true>), dim3(nb), dim3(kNeThreads), 0, s, Q, (_Float16 *)nullptr,
-                           (float *)nullptr, part, h.kparams<double>(h.t0), h.kparams<float>(h.t0), step_grid(h));
+        const Around a = around(h, kTiled);
+        const unsigned nb = std::min(a.tiles, (unsigned)(2 * kRedBlocks));
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(nb), dim3(kNeThreads), 0, s, Q, (_Float16 *)nullptr, (float *)nullptr, part,
+                               h.kparams<double>(h.t0), h.kparams<float>(h.t0), a.tiles);
+        };
+        a.tiled ? go(k_init_ne<Sys, Lat, true, kTiled>) : go(k_init_ne<Sys, Lat, true, false>);
         combine(part, Sys::K, nb, 1, s);
         return hipGetLastError();
     }
     static hipError_t moments(const lbm_state_impl &h, const void *fin, void *out, int absolute, int out_dtype,
                               hipStream_t s)
     {
-        const KParams<float> p = h.kparams<float>(h.t0);
-        const KParams<double> pd = h.kparams<double>(h.t0);
+        const Around a = around(h, kTiledMoments);
+        auto go = [&](auto kern, auto *to) {
+            hipLaunchKernelGGL(kern, dim3(a.tiles), dim3(kNeThreads), 0, s, gp(h, fin), mp(h, fin), to,
+                               h.kparams<float>(h.t0), h.kparams<double>(h.t0), absolute);
+        };
         if (out_dtype == 0)
-            hipLaunchKernelGGL((k_moments_ne<Sys, Lat, double>), dim3(step_grid(h)), dim3(kNeThreads), 0, s, gp(h, fin),
-                               mp(h, fin), (double *)out, p, pd, absolute);
+            a.tiled ? go(k_moments_ne<Sys, Lat, double, kTiledMoments>, (double *)out)
+                    : go(k_moments_ne<Sys, Lat, double, false>, (double *)out);
         else
-            hipLaunchKernelGGL((k_moments_ne<Sys, Lat, float>), dim3(step_grid(h)), dim3(kNeThreads), 0, s, gp(h, fin),
-                               mp(h, fin), (float *)out, p, pd, absolute);
+            a.tiled ? go(k_moments_ne<Sys, Lat, float, kTiledMoments>, (float *)out)
+                    : go(k_moments_ne<Sys, Lat, float, false>, (float *)out);
         return hipGetLastError();
     }
     static hipError_t reduce(const lbm_state_impl &h, const void *fin, int what, const double *ref, double *aux,
@@ -699,9 +788,13 @@ struct ImplNE {
     {
         const int nslot = (what == 3 || what == 4) ? 1 : (what == 0 ? Sys::K : 2 * Sys::K);
         const int is_max = (what == 2 || what == 3) ? 1 : 0;
-        const unsigned nb = std::min(step_grid(h), (unsigned)std::min(2 * kRedBlocks, 2 * LBM_MAXK * kRedBlocks / nslot));
-        hipLaunchKernelGGL((k_reduce1_ne<Sys, Lat>), dim3(nb), dim3(kNeThreads), 0, s, gp(h, fin), mp(h, fin), ref, aux,
-                           h.kparams<float>(h.t0), h.kparams<double>(h.t0), what, step_grid(h));
+        const Around a = around(h, kTiled);
+        const unsigned nb = std::min(a.tiles, (unsigned)std::min(2 * kRedBlocks, 2 * LBM_MAXK * kRedBlocks / nslot));
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3(nb), dim3(kNeThreads), 0, s, gp(h, fin), mp(h, fin), ref, aux,
+                               h.kparams<float>(h.t0), h.kparams<double>(h.t0), what, a.tiles);
+        };
+        a.tiled ? go(k_reduce1_ne<Sys, Lat, kTiled>) : go(k_reduce1_ne<Sys, Lat, false>);
         combine(aux, nslot, nb, is_max, s);
         return hipGetLastError();
     }
