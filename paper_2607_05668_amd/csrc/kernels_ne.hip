@@ -94,13 +94,8 @@ __device__ inline int pmod(int v, int n)
     return r < n ? r : (r < 2 * n ? r - n : r % n);
 }
 
-// Least wavefronts a SIMD.  Six fields on D2Q9 take 130 registers, two more than
-// leave room for a fourth wavefront; held to 128, three values go to scratch
-// (512^2: 18.3 -> 16.4 us per step).
-template <class Sys, class Lat> constexpr int ne_waves() { return Sys::K == 6 && Lat::Q == 9 ? 4 : 1; }
-
 template <class Sys, class Lat, bool NT, bool O32>
-__global__ __launch_bounds__(kNeTX * kNeTY, (ne_waves<Sys, Lat>())) void k_step_ne(const _Float16 *__restrict__ gin,
+__global__ __launch_bounds__(kNeTX * kNeTY) void k_step_ne(const _Float16 *__restrict__ gin,
                                                            const float *__restrict__ Min,
                                                            _Float16 *__restrict__ gout, float *__restrict__ Mout,
                                                            const KParams<float> p)
