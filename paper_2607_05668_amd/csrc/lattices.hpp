@@ -94,17 +94,30 @@ __host__ __device__ constexpr int lat_c(int i, int a)
 // needed).  The zeroth part takes the moment as an unevaluated sum
 // dQ = hi + lo (compensated summation), w_i dQ = w_i hi + w_i lo.
 // `zeroth` gives w_i s for i >= 1 (used for the source term).
+// Where the products are by powers of two, and so exact, they may be fused
+// into the sums wherever the compiler likes: no bit depends on it.  (With
+// multiply-adds within expressions only, the deviations' step of six fields on
+// D2Q9 takes 130 registers in place of 128 and a SIMD three wavefronts in place
+// of four: neo-Hookean 512^2 18.5 against 16.5 us per step, 100000 x 20 264
+// against 228.)
+#define LBM_EXACT_PRODUCTS _Pragma("clang fp contract(fast)")
 template <class L> struct ExactEq;
 
 template <> struct ExactEq<D2Q5> {
     template <class R> __host__ __device__ static R rest(R M) { return div_by<3>(M); }
-    template <class R> __host__ __device__ static R amp(R qh, R ql) { return qh * R(0.5) + ql * R(0.5); }
+    template <class R> __host__ __device__ static R amp(R qh, R ql)
+    {
+        LBM_EXACT_PRODUCTS
+        return qh * R(0.5) + ql * R(0.5);
+    }
     template <class R> __host__ __device__ static R comb(R A, R hx, R hy, int i)
     {
+        LBM_EXACT_PRODUCTS
         return i == 1 ? A + hx : (i == 2 ? A + hy : (i == 3 ? A - hx : A - hy));
     }
     template <class R> __host__ __device__ static void feq(R hi, R lo, const R *G, R *e)
     {
+        LBM_EXACT_PRODUCTS
         const R A = amp(div_by<3>(hi), div_by<3>(lo)), hx = G[0] * R(0.5), hy = G[1] * R(0.5);
 #pragma unroll
         for (int i = 1; i < 5; ++i) e[i] = comb(A, hx, hy, i);
@@ -115,6 +128,7 @@ template <> struct ExactEq<D2Q5> {
     // dir(parts(M, G), i) equals feq(M, 0, G)[i] bit for bit.
     template <class R> __host__ __device__ static void parts(R M, const R *G, R *P)
     {
+        LBM_EXACT_PRODUCTS
         P[0] = div_by<3>(M); P[1] = G[0] * R(0.5); P[2] = G[1] * R(0.5);
     }
     template <class R> __host__ __device__ static R rest_parts(const R *P) { return P[0]; }
@@ -130,10 +144,19 @@ template <> struct ExactEq<D2Q5> {
 };
 
 template <> struct ExactEq<D2Q9> {
-    template <class R> __host__ __device__ static R rest(R M) { return div_by<9>(M) * R(4); }
-    template <class R> __host__ __device__ static R amp(R qh, R ql) { return qh * R(0.25) + ql * R(0.25); }
+    template <class R> __host__ __device__ static R rest(R M)
+    {
+        LBM_EXACT_PRODUCTS
+        return div_by<9>(M) * R(4);
+    }
+    template <class R> __host__ __device__ static R amp(R qh, R ql)
+    {
+        LBM_EXACT_PRODUCTS
+        return qh * R(0.25) + ql * R(0.25);
+    }
     template <class R> __host__ __device__ static R comb(R A, R gx, R gy, int i)
     {
+        LBM_EXACT_PRODUCTS
         const R A4 = A * R(4);
         switch (i) {
         case 1: return A4 + gx;
@@ -158,7 +181,11 @@ template <> struct ExactEq<D2Q9> {
     {
         P[0] = div_by<9>(M); P[1] = div_by<3>(G[0]); P[2] = div_by<3>(G[1]);
     }
-    template <class R> __host__ __device__ static R rest_parts(const R *P) { return P[0] * R(4); }
+    template <class R> __host__ __device__ static R rest_parts(const R *P)
+    {
+        LBM_EXACT_PRODUCTS
+        return P[0] * R(4);
+    }
     template <class R> __host__ __device__ static R dir(const R *P, int i)
     {
         return comb(amp(P[0], div_by<9>(R(0))), P[1], P[2], i);

@@ -63,3 +63,9 @@ def test_single_steps_in_double_leave_two_wavefronts_a_simd(kernels, state):
 def test_single_steps_of_the_largest_states_spill_no_more(kernels, state, scratch):
     for name, (_, spilled) in _single_steps_in_double(kernels, *state):
         assert spilled <= scratch, (name, spilled)
+
+
+# four wavefronts a SIMD hold 128 registers each
+def test_single_step_of_the_deviations_leaves_four_wavefronts_a_simd(kernels):
+    for name, (registers, scratch) in _matching(kernels, "k_step_ne", "SysNeoHooke", "D2Q9", "").items():
+        assert registers <= 128 and scratch <= 32, (name, registers, scratch)
