@@ -119,6 +119,6 @@ int march_steps(const StepState &s, int most, int lds_most, int lds_two, Halo &&
     const double single = 0.97 * single_step_us(s, nx, ny);
     if (most > 2 && want >= most && !(most == 3 && want == 4) && march_us(s, most, halo(most), lds_most, nx, ny) <= single)
         return most;
-    const double gain = want == 3 ? 0.7 : (most > 2 ? 0.9 : 1.0);
+    const double gain = want == 3 ? 0.55 : (most > 2 ? 0.9 : 1.0);
     return march_us(s, 2, halo(2), lds_two, nx, ny) <= gain * single ? 2 : 1;
 }
