@@ -70,8 +70,8 @@ struct Cell {
     // for Euler on D2Q5 (150 x 101 shallow water: 5.6 -> 4.6 us per step).
     // The other systems evaluate their flux in float, as their registers
     // allow, and form moments, equilibria and relaxation in double (WIDEQ: 3D
-    // NSF 3714 -> 2407 vector instructions, 75 x 66 x 50: 38.2 -> 35.0 us per
-    // step).  The 3D steps beyond the cache do not (see k_step).
+    // NSF 3714 -> 2407 vector instructions, 75 x 66 x 50: 40.0 -> 37.5 us per
+    // step; at 256^3, bound by memory, 2745 -> 2780).
     static constexpr bool WIDE = Sys::precise && std::is_same<St, float>::value;
     // The 3D velocity-gradient trackers need the accuracy: they see the
     // momentum's rounding amplified by |u| / |du| and by 1 / (k dx), and with

@@ -212,8 +212,7 @@ template <> struct ExactEq<D3Q7> {
     }
 };
 
-// Float-float form of the same equilibrium, for the double-precision steppers
-// and the 3D steps in float beyond the cache:
+// Float-float form of the same equilibrium, for the double-precision steppers:
 // every quantity is an unevaluated pair (hi, lo) built with error-free
 // transformations (two-sum; exact division remainder r = a - q b and exact
 // product error via fused multiply-add), so that e_i carries no rounding
@@ -281,19 +280,5 @@ template <> struct ExactEqFF<D2Q9> {
         const FF<R> sp = ff_scale(ff_add(gx, gy), R(0.25)), sm = ff_scale(ff_add(gy, mgx), R(0.25));
         e[5] = ff_add(A, sp); e[6] = ff_add(A, sm);
         e[7] = ff_add(A, FF<R>{-sp.hi, -sp.lo}); e[8] = ff_add(A, FF<R>{-sm.hi, -sm.lo});
-    }
-};
-
-template <> struct ExactEqFF<D3Q7> {
-    template <class R>
-    __host__ __device__ static void feq(R qh, R ql, const R *Gh, const R *Gl, FF<R> *e)
-    {
-        const FF<R> A = {qh * R(0.125), ql * R(0.125)};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const FF<R> h = {Gh[a] * R(0.5), Gl[a] * R(0.5)};
-            e[1 + 2 * a] = ff_add(A, h);
-            e[2 + 2 * a] = ff_add(A, FF<R>{-h.hi, -h.lo});
-        }
     }
 };

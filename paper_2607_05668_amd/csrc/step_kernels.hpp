@@ -240,14 +240,7 @@ __global__ __launch_bounds__((step_block<Sys, St>())) void k_step(const St *__re
     auto emit = [&](int k, int i, St v) {
         st_pop<NT>(byte_at(fout + (size_t)z * slab + (size_t)(k * Q + i) * kTile, own), v);
     };
-    // The 3D steps in float form their equilibria in double where their state
-    // fits the last-level cache, and in float-float beyond it.  There HBM bounds
-    // them, and the float-float form's 1300 instructions more, between the loads
-    // and the stores, do not cost but gain a little: 17 fields with the
-    // manufactured forcing 256^3 2736 us per step, 2771 in double; 75 x 66 x 50
-    // 38.2 and 35.0, 64^3 41.5 and 38.7.
-    constexpr bool FLOAT_FLOAT = D == 3 && NT && std::is_same<St, float>::value;
-    if constexpr ((C::WIDE || C::WIDEQ) && !FLOAT_FLOAT) {
+    if constexpr (C::WIDE || C::WIDEQ) {
         C::update(p, f, ex, Smms, dQ, emit);
     } else {
 #include "collide_plain.inc"
