@@ -682,9 +682,9 @@ struct ImplNE {
     }
     // several steps per launch (k_march_ne) where that pays (march_plan.hpp)
     static constexpr int kMost = ne_march_most<Sys, Lat>();
-    static int steps_per_launch(const lbm_state_impl &h, int want, bool)
+    static int steps_per_launch(const lbm_state_impl &h, int want)
     {
-        const StepState s = {3, Sys::K, Lat::Q, false, h.field_b != nullptr, false};
+        const StepState s = {3, Sys::K, Lat::Q, false, h.field_b != nullptr};
         return march_steps(s, kMost, ne_march_lds<Sys, Lat>(kMost), ne_march_lds<Sys, Lat>(2), [](int T) { return T; }, want,
                            h.nx, h.ny);
     }

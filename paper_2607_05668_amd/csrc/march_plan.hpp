@@ -62,7 +62,6 @@ struct StepState {
     int fields, velocities;
     bool two_rates;                 // two-relaxation-time collision
     bool sources;                   // coefficient or source fields are read
-    bool record;                    // every step's moments are stored
 };
 // us: a launch, a population's row (loads and stores) and stage of a wavefront
 // that has its SIMD to itself, and the least time of a single step per population
@@ -101,8 +100,11 @@ inline double march_us(const StepState &s, int T, int halo, int lds, int nx, int
     const double share = (waves <= kSimds + kSimds / 20 ? 1.0 : 1.4) * (double)((waves - 1) / two + 1);
     const StepCosts &c = kStepCosts[s.storage];
     double work = n * (c.row * (rows + 2 * halo) + c.stage * T * (rows + halo));
-    work *= s.two_rates ? 1.25 : (s.sources ? 1.1 : 1.0);
-    if (s.record) work += 0.11 * s.fields * T * (rows + 2 * halo);
+    // kernels that read fields, and those of two rates (they read them too); fitted
+    // to 608 grids and states each.  us per step, one step a launch / two in a
+    // march: advection-diffusion D2Q9 600 x 512 with two rates in double 21.8 / 19.4
+    if (s.two_rates) work *= s.storage == 1 ? 1.3 : 1.0;
+    else if (s.sources) work *= s.storage < 2 ? 1.2 : 1.1;
     return (c.launch + std::max(share * work, memory_us(state_bytes(s, nx, ny)))) / T;
 }
 

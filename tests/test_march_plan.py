@@ -94,7 +94,7 @@ def test_marches_are_taken_where_they_were_measured_faster(tmp_path):
     out = run(tmp_path, "const int m[][9] = {" + ", ".join(rows) + "};" + r"""
     int wrong = 0;
     for (auto &r : m) {
-        const StepState s = {r[0], r[1], r[2], false, false, false};
+        const StepState s = {r[0], r[1], r[2], false, false};
         auto halo = [&](int T) { return r[0] == 3 ? T : T - 1; };
         const int n = march_steps(s, r[3], r[4], r[5], halo, 40, r[7], r[6]);
         if ((n > 1) != (r[8] != 0) || (n > 1 && n != r[3] && n != 2)) {
@@ -105,5 +105,12 @@ def test_marches_are_taken_where_they_were_measured_faster(tmp_path):
         if (march_steps(s, r[3], r[4], r[5], halo, 1, r[7], r[6]) != 1) ++wrong;
         if (march_steps(s, r[3], r[4], r[5], halo, 40, 0x7fffffff / 8, 4) != 1) ++wrong;
     }
+    // the recomputation of a 512^2 rollout, with topography and history: 8.6 us per
+    // step in the march, 10.4 by single steps
+    const StepState rollout = {1, 3, 9, false, true};
+    if (march_steps(rollout, 4, 20744, 6920, [](int T) { return T - 1; }, 40, 512, 512) != 4) ++wrong;
+    // advection-diffusion with two rates in double, 600 x 512: 19.4 and 21.8 us
+    const StepState rates = {0, 3, 9, true, false};
+    if (march_steps(rates, 2, 13840, 13840, [](int T) { return T - 1; }, 40, 512, 600) != 2) ++wrong;
     printf("%d\n", wrong);""")
     assert out == "0\n", out
