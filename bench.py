@@ -37,7 +37,8 @@ KERNEL_SOURCES = ["paper_2607_05668_amd/csrc/step_kernels.hpp", "paper_2607_0566
                   "paper_2607_05668_amd/csrc/kernels.hip", "paper_2607_05668_amd/csrc/systems.hpp",
                   "paper_2607_05668_amd/csrc/lattices.hpp", "paper_2607_05668_amd/csrc/impl.hpp",
                   "paper_2607_05668_amd/csrc/dual.hpp", "paper_2607_05668_amd/csrc/device_common.hpp",
-                  "paper_2607_05668_amd/csrc/collide.hpp"]
+                  "paper_2607_05668_amd/csrc/collide.hpp", "paper_2607_05668_amd/csrc/collide_plain.inc",
+                  "paper_2607_05668_amd/csrc/march.hpp", "paper_2607_05668_amd/csrc/march_plan.hpp"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_nsf256.json")
 
 

@@ -3,6 +3,7 @@ without touching a GPU, and the committed HBM-traffic record it reads is
 self-consistent."""
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -44,3 +45,18 @@ def test_stale_traffic_record_is_not_reported(tmp_path, monkeypatch):
     p.write_text(json.dumps(t))
     monkeypatch.setattr(bench, "TRAFFIC_FILE", str(p))
     assert bench.measured_traffic() is None
+
+
+def test_traffic_record_covers_every_source_of_its_kernel():
+    """A change to any file that the benchmark's kernel is compiled from makes
+    the record stale."""
+    csrc = os.path.join(ROOT, "paper_2607_05668_amd", "csrc")
+    left, seen = ["sys_nsf17.hip"], set()
+    while left:
+        name = left.pop()
+        if name not in seen:
+            seen.add(name)
+            with open(os.path.join(csrc, name)) as fh:
+                left += re.findall(r'^\s*#include "([^"]+)"', fh.read(), re.M)
+    seen = {n for n in seen if os.path.dirname(os.path.normpath(os.path.join(csrc, n))) == csrc}
+    assert seen <= {os.path.basename(f) for f in bench.KERNEL_SOURCES}, seen
