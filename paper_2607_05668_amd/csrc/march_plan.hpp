@@ -54,7 +54,8 @@ inline int march_rows(int halo, int lds, int populations, int nx, int ny)
 // to 13%, the single step mostly to 15%).  Against the single step, two launches
 // of a hundred end up slower, by at most 19%, on grids a few rows high; by a
 // rule on rows alone a march was up to 22 times slower (200000 rows of one
-// cell) and 1.2-1.4 times for binary16 at 512^2.  us per step, one step a
+// cell) and 1.2-1.4 times for binary16 at 512^2.  A moment history costs both
+// about the same (1443 pairs) and decides nothing.  us per step, one step a
 // launch / march: shallow water D2Q9 float 512^2 9.6 / 7.0, 200000 x 1
 // 8.9 / 120; binary16 512^2 6.3 / 8.4, 2048^2 77.8 / 50.1.
 struct StepState {

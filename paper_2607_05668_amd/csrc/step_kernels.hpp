@@ -13,11 +13,13 @@
 // k_step advances one step: one thread updates one cell, loading its K*Q
 // populations (a1), colliding them (a2 to a6, collide.hpp) and storing them
 // aligned (a7), so every population is read once and written once per step.
-// Runs of two steps and more in 2D take the kernel of march.hpp instead, which
-// does so once for up to four steps.  The workgroup index of k_step is
-// remapped so that consecutive tiles of cells run on the same XCD (the
-// hardware dispatches workgroups round-robin over the 8 XCDs, each with its
-// own L2), keeping the rows that neighbouring tiles share in one L2.
+// Runs of two steps and more in 2D take the kernels of march.hpp where those
+// are faster (steps_per_launch): squares of a small grid do so once for up to
+// five steps, strips of a larger one for up to four.  3D, the regularized
+// collision, states of more than seven fields and flat grids stay with k_step.
+// Its workgroup index is remapped so that consecutive tiles of cells run on the
+// same XCD (the hardware dispatches workgroups round-robin over the 8 XCDs, each
+// with its own L2), keeping the rows that neighbouring tiles share in one L2.
 #pragma once
 
 #include <hip/hip_runtime.h>
