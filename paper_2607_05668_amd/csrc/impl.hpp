@@ -76,9 +76,9 @@ struct lbm_state_impl;
 struct Launchers {
     int K, Q, D;
     size_t store_bytes;               // bytes per stored population
-    // steps that the next launch advances when `want` are left, and that launch
-    // (step for one, multi for more; qhist: one slice per step)
-    int (*steps_per_launch)(const lbm_state_impl &, int want);
+    // steps that the next launch advances when `want` of a run's `run` steps are
+    // left, and that launch (step for one, multi for more; qhist: one slice per step)
+    int (*steps_per_launch)(const lbm_state_impl &, int want, int run);
     hipError_t (*step)(const lbm_state_impl &, const void *fin, void *fout, void *qhist, hipStream_t);
     hipError_t (*multi)(const lbm_state_impl &, int steps, const void *fin, void *fout, void *qhist, hipStream_t);
     // speed: reduction scratch or null; gets the largest wave speed in the

@@ -682,11 +682,11 @@ struct ImplNE {
     }
     // several steps per launch (k_march_ne) where that pays (march_plan.hpp)
     static constexpr int kMost = ne_march_most<Sys, Lat>();
-    static int steps_per_launch(const lbm_state_impl &h, int want)
+    static int steps_per_launch(const lbm_state_impl &h, int want, int run)
     {
         const StepState s = {3, Sys::K, Lat::Q, false, h.field_b != nullptr};
         return march_steps(s, kMost, ne_march_lds<Sys, Lat>(kMost), ne_march_lds<Sys, Lat>(2), [](int T) { return T; }, want,
-                           h.nx, h.ny);
+                           run, h.nx, h.ny);
     }
     template <int T>
     static hipError_t launch_march(const lbm_state_impl &h, const void *fin, void *fout, hipStream_t s)

@@ -784,14 +784,15 @@ static int check_finite(lbm_state *h)
 static hipError_t enqueue_steps(lbm_state *h, int &left, char *qhist, size_t stride, int &cur, hipStream_t s,
                                 bool captured)
 {
+    const int run = left;
     bool halve = false;
     for (int l = captured ? left : 0; l > 0;) {
-        const int m = h->L->steps_per_launch(*h, l);
+        const int m = h->L->steps_per_launch(*h, l, run);
         halve ^= m % 2 == 0;
         l -= m;
     }
     for (int half = 0; left > 0;) {
-        int m = half ? half : h->L->steps_per_launch(*h, left);
+        int m = half ? half : h->L->steps_per_launch(*h, left, run);
         half = 0;
         if (halve && m % 2 == 0) {
             half = m /= 2;
@@ -820,7 +821,7 @@ static int run_steps(lbm_state *h, int n, void *qhist)
             const GraphKey key = {0, len, h->cur, h->epoch, {h->pop[0], h->pop[1], q0, nullptr}};
             const int cur0 = h->cur;
             int cur = cur0;
-            for (int left = len; left > 0; cur ^= 1) left -= h->L->steps_per_launch(*h, left);
+            for (int left = len; left > 0; cur ^= 1) left -= h->L->steps_per_launch(*h, left, len);
             rc = replay(h, key, [&](hipStream_t s) {
                 int c = cur0, left = len;
                 return enqueue_steps(h, left, q0, stride, c, s, false);

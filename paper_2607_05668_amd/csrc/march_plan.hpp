@@ -109,19 +109,21 @@ inline double march_us(const StepState &s, int T, int halo, int lds, int nx, int
     return (c.launch + std::max(share * work, memory_us(state_bytes(s, nx, ny)))) / T;
 }
 
-// Steps of the next launch when `want` are left: `most` (LDS lds_most) or two
-// (LDS lds_two) in a march, or one.  Strips less than half full never pay
-// against the 64-cell tiles of the single step by much.  Three steps as two and
-// one have to gain more: the single step finds what the march left in the L2 of
-// other XCDs (shallow water D2Q9 double 512^2, three steps: 67 us in place of 56
-// for the two kernels by themselves).  halo(T): rows lost.
+// Steps of the next launch when `want` of a run's `run` steps are left: `most`
+// (LDS lds_most) or two (LDS lds_two) in a march, or one; launches of one step
+// come last.  Strips less than half full never pay against the 64-cell tiles of
+// the single step by much.  A run of three as two and one has to gain more: a
+// march and a single step next to each other find what the other left in the L2
+// of other XCDs (us per step of runs of three, double 512^2, single steps / with
+// a march of two: neo-Hookean D2Q5 20.6 / 25.0, Euler D2Q9 24.1 / 28.7).
+// halo(T): rows lost.
 template <class Halo>
-int march_steps(const StepState &s, int most, int lds_most, int lds_two, Halo &&halo, int want, int nx, int ny)
+int march_steps(const StepState &s, int most, int lds_most, int lds_two, Halo &&halo, int want, int run, int nx, int ny)
 {
     if (want < 2 || most < 2 || nx < 32 || !march_fits(nx, ny, s.fields * s.velocities, kStepBytes[s.storage])) return 1;
-    const double single = 0.97 * single_step_us(s, nx, ny);
-    if (most > 2 && want >= most && !(most == 3 && want == 4) && march_us(s, most, halo(most), lds_most, nx, ny) <= single)
+    const double single = 0.97 * single_step_us(s, nx, ny), gain = run == 3 ? 0.55 : (most > 2 ? 0.9 : 1.0);
+    const bool two = march_us(s, 2, halo(2), lds_two, nx, ny) <= gain * single;
+    if (most > 2 && want >= most && !(most == 3 && want == 4 && two) && march_us(s, most, halo(most), lds_most, nx, ny) <= single)
         return most;
-    const double gain = want == 3 ? 0.55 : (most > 2 ? 0.9 : 1.0);
-    return march_us(s, 2, halo(2), lds_two, nx, ny) <= gain * single ? 2 : 1;
+    return two ? 2 : 1;
 }

@@ -751,9 +751,9 @@ struct Impl {
         }
         return 0;
     }
-    // Steps of the next launch when `want` are left (1: k_step): squares on small
-    // grids, else a march where it pays (march_plan.hpp).
-    static int steps_per_launch(const lbm_state_impl &h, int want)
+    // Steps of the next launch when `want` of a run's `run` are left (1: k_step):
+    // squares on small grids, else a march where it pays (march_plan.hpp).
+    static int steps_per_launch(const lbm_state_impl &h, int want, int run)
     {
         if constexpr (kMarch) {
             if (want < 2 || h.regularized) return 1;
@@ -761,7 +761,7 @@ struct Impl {
             constexpr int storage = std::is_same<St, double>::value ? 0 : (std::is_same<St, float>::value ? 1 : 2);
             const StepState s = {storage, Sys::K, Lat::Q, h.trt_lambda > 0, h.field_b || h.field_src};
             return march_steps(s, kMost, march_lds<Sys, Lat, St>(kMost), march_lds<Sys, Lat, St>(2), [](int T) { return T - 1; },
-                               want, h.nx, h.ny);
+                               want, run, h.nx, h.ny);
         }
         return 1;
     }

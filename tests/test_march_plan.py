@@ -96,21 +96,58 @@ def test_marches_are_taken_where_they_were_measured_faster(tmp_path):
     for (auto &r : m) {
         const StepState s = {r[0], r[1], r[2], false, false};
         auto halo = [&](int T) { return r[0] == 3 ? T : T - 1; };
-        const int n = march_steps(s, r[3], r[4], r[5], halo, 40, r[7], r[6]);
+        const int n = march_steps(s, r[3], r[4], r[5], halo, 40, 40, r[7], r[6]);
         if ((n > 1) != (r[8] != 0) || (n > 1 && n != r[3] && n != 2)) {
             printf("storage %d, %d fields, %d x %d: %d steps a launch\n", r[0], r[1], r[6], r[7], n);
             ++wrong;
         }
         // one step left, and what the kernels do not hold
-        if (march_steps(s, r[3], r[4], r[5], halo, 1, r[7], r[6]) != 1) ++wrong;
-        if (march_steps(s, r[3], r[4], r[5], halo, 40, 0x7fffffff / 8, 4) != 1) ++wrong;
+        if (march_steps(s, r[3], r[4], r[5], halo, 1, 1, r[7], r[6]) != 1) ++wrong;
+        if (march_steps(s, r[3], r[4], r[5], halo, 40, 40, 0x7fffffff / 8, 4) != 1) ++wrong;
     }
     // the recomputation of a 512^2 rollout, with topography and history: 8.6 us per
     // step in the march, 10.4 by single steps
     const StepState rollout = {1, 3, 9, false, true};
-    if (march_steps(rollout, 4, 20744, 6920, [](int T) { return T - 1; }, 40, 512, 512) != 4) ++wrong;
+    if (march_steps(rollout, 4, 20744, 6920, [](int T) { return T - 1; }, 40, 40, 512, 512) != 4) ++wrong;
     // advection-diffusion with two rates in double, 600 x 512: 19.4 and 21.8 us
     const StepState rates = {0, 3, 9, true, false};
-    if (march_steps(rates, 2, 13840, 13840, [](int T) { return T - 1; }, 40, 512, 600) != 2) ++wrong;
+    if (march_steps(rates, 2, 13840, 13840, [](int T) { return T - 1; }, 40, 40, 512, 600) != 2) ++wrong;
     printf("%d\n", wrong);""")
     assert out == "0\n", out
+
+
+def test_launches_of_one_step_come_last(tmp_path):
+    """Every run of up to 70 steps of every state and many grids: its launches
+    add up, and none of one step comes before a larger one."""
+    out = run(tmp_path, r"""
+    for (int storage = 0; storage < 4; ++storage)
+        for (int q : {5, 9})
+            for (int k = 1; k <= (storage == 3 ? 12 : 7); ++k)
+                for (int most = 2; most <= 4; ++most)
+                    for (int ny : {3, 60, 200, 450, 512, 1000, 2048, 100000})
+                        for (int nx : {20, 64, 300, 512, 1100, 2048}) {
+                            const StepState s = {storage, k, q, false, false};
+                            const int e = storage == 0 ? 8 : storage == 2 ? 2 : 4, extra = storage == 3 ? 0 : -1;
+                            auto lds = [&](int T) { return ((T + extra) * (q == 9 ? 9 : 5) * k * 64 + 2) * e; };
+                            if (lds(most) > kLdsPerCu / 5) continue;
+                            auto halo = [&](int T) { return storage == 3 ? T : T - 1; };
+                            for (int n = 1; n <= 70; ++n) {
+                                int left = n, last = most + 1;
+                                while (left > 0) {
+                                    const int m = march_steps(s, most, lds(most), lds(2), halo, left, n, nx, ny);
+                                    const bool late = last == 1 && m > 1;
+                                    if (m < 1 || m > left || late) {
+                                        printf("storage %d, %d fields, %d velocities, %d x %d, run of %d, %d left: %d steps after %d\n",
+                                               storage, k, q, ny, nx, n, left, m, last);
+                                        return 1;
+                                    }
+                                    last = m, left -= m;
+                                }
+                            }
+                        }
+    // a run of three that gains little from its march takes single steps
+    const StepState s = {0, 3, 9, false, false};
+    for (int left = 3; left > 0; --left)
+        if (march_steps(s, 2, 13840, 13840, [](int T) { return T - 1; }, left, 3, 512, 512) != 1) return 1;
+    puts("ok");""")
+    assert out == "ok\n"
