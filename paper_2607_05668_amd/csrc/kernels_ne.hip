@@ -404,37 +404,55 @@ struct NeCells {
             x = (int)(cell - (size_t)y * p.nx);
         }
     }
-    // e_i of the sender x - c_i, every field
+    // take(k, i, e_i of field k of the sender x - c_i), every field's i in order.
+    // TILED: field by field, which keeps one field's values at a time (direction
+    // by direction k_moments_ne takes 100 registers in place of 72 for the
+    // neo-Hookean D2Q9, one wavefront a SIMD fewer: 171 against 155 us at 2048^2).
+    template <class Moment, class Take>
+    __device__ __forceinline__ void each(Moment &&moment, Take &&take) const
+    {
+        if constexpr (TILED) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const float *const part = parts + k * 3 * kNeHalo;
+#pragma unroll
+                for (int i = 0; i < Lat::Q; ++i) {
+                    const int h = (ly + 1 - Lat::cy[i]) * kNeHX + (lx + 1 - Lat::cx[i]);
+                    const float Pt[3] = {part[h], part[kNeHalo + h], part[2 * kNeHalo + h]};
+                    take(k, i, i == 0 ? ExactEq<Lat>::rest_parts(Pt) : ExactEq<Lat>::dir(Pt, i));
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < Lat::Q; ++i) {
+                float e[K];
+                sent(i, moment, e);
+#pragma unroll
+                for (int k = 0; k < K; ++k) take(k, i, e[k]);
+            }
+        }
+    }
+    // e_i of the sender x - c_i, every field, from its moments
     template <class Moment>
     __device__ __forceinline__ void sent(int i, Moment &&moment, float *e) const
     {
-        if constexpr (TILED) {
-            const int h = (ly + 1 - Lat::cy[i]) * kNeHX + (lx + 1 - Lat::cx[i]);
+        const size_t c = (size_t)wrapi(y - Lat::cy[i], p.ny) * p.nx + wrapi(x - Lat::cx[i], p.nx);
+        float M[K], P[K][D];
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const float Pt[3] = {parts[k * 3 * kNeHalo + h], parts[(k * 3 + 1) * kNeHalo + h],
-                                     parts[(k * 3 + 2) * kNeHalo + h]};
-                e[k] = i == 0 ? ExactEq<Lat>::rest_parts(Pt) : ExactEq<Lat>::dir(Pt, i);
-            }
-        } else {
-            const size_t c = (size_t)wrapi(y - Lat::cy[i], p.ny) * p.nx + wrapi(x - Lat::cx[i], p.nx);
-            float M[K], P[K][D];
+        for (int k = 0; k < K; ++k) M[k] = moment(k, c);
+        if (i == 0) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) M[k] = moment(k, c);
-            if (i == 0) {
+            for (int k = 0; k < K; ++k) e[k] = ExactEq<Lat>::rest(M[k]);
+            return;
+        }
+        Sys::template flux_delta<float, float>(p.phys, M, P);
 #pragma unroll
-                for (int k = 0; k < K; ++k) e[k] = ExactEq<Lat>::rest(M[k]);
-                return;
-            }
-            Sys::template flux_delta<float, float>(p.phys, M, P);
+        for (int k = 0; k < K; ++k) {
+            float G[D], all[Lat::Q];
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                float G[D], all[Lat::Q];
-#pragma unroll
-                for (int a = 0; a < D; ++a) G[a] = p.lam * P[k][a];
-                ExactEq<Lat>::feq(M[k], 0.0f, G, all);
-                e[k] = all[i];
-            }
+            for (int a = 0; a < D; ++a) G[a] = p.lam * P[k][a];
+            ExactEq<Lat>::feq(M[k], 0.0f, G, all);
+            e[k] = all[i];
         }
     }
     // before the next tile's enter
@@ -450,14 +468,9 @@ struct NeCells {
         pulled_places_of<K, Lat, unsigned long long>(x, y, 0, p.nx, p.ny, 1, src);
 #pragma unroll
         for (int k = 0; k < K; ++k) q[k] = 0.0;
-#pragma unroll
-        for (int i = 0; i < Lat::Q; ++i) {
-            float e[K];
-            sent(i, moment, e);
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-                q[k] += (double)fmaf((float)g[src[i] + (size_t)(k * Lat::Q * kTile)], p.inv_scale[k], e[k]);
-        }
+        each(moment, [&](int k, int i, float e) __attribute__((always_inline)) {
+            q[k] += (double)fmaf((float)g[src[i] + (size_t)(k * Lat::Q * kTile)], p.inv_scale[k], e);
+        });
     }
 };
 
@@ -496,25 +509,19 @@ __global__ __launch_bounds__(kNeThreads) void k_init_ne(const double *__restrict
             pulled_places_of<K, Lat, unsigned long long>(at.x, at.y, 0, pd.nx, pd.ny, 1, dst);
 #pragma unroll
             for (int k = 0; k < K; ++k) q[k] = 0.0;
+            at.each(moment, [&](int k, int i, float e) __attribute__((always_inline)) {
+                double cd = 0.0;
 #pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                float e[K];
-                at.sent(i, moment, e);
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    double cd = 0.0;
-#pragma unroll
-                    for (int a = 0; a < D; ++a) cd += lat_c<Lat>(i, a) * P[k][a];
-                    const double gv = Lat::w[i] * (dq[k] + pd.lam_cs2 * cd) - (double)e[k];
-                    if constexpr (SCALE) {
-                        mx[k] = fabs(gv) > mx[k] ? fabs(gv) : mx[k];
-                    } else {
-                        const _Float16 v = (_Float16)(gv * (double)pf.scale[k]);
-                        g[dst[i] + (size_t)(k * Q * kTile)] = v;
-                        q[k] += (double)fmaf((float)v, pf.inv_scale[k], e[k]);
-                    }
+                for (int a = 0; a < D; ++a) cd += lat_c<Lat>(i, a) * P[k][a];
+                const double gv = Lat::w[i] * (dq[k] + pd.lam_cs2 * cd) - (double)e;
+                if constexpr (SCALE) {
+                    mx[k] = fabs(gv) > mx[k] ? fabs(gv) : mx[k];
+                } else {
+                    const _Float16 v = (_Float16)(gv * (double)pf.scale[k]);
+                    g[dst[i] + (size_t)(k * Q * kTile)] = v;
+                    q[k] += (double)fmaf((float)v, pf.inv_scale[k], e);
                 }
-            }
+            });
             if constexpr (!SCALE) {
 #pragma unroll
                 for (int k = 0; k < K; ++k) {

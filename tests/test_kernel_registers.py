@@ -69,3 +69,12 @@ def test_single_steps_of_the_largest_states_spill_no_more(kernels, state, scratc
 def test_single_step_of_the_deviations_leaves_four_wavefronts_a_simd(kernels):
     for name, (registers, scratch) in _matching(kernels, "k_step_ne", "SysNeoHooke", "D2Q9", "").items():
         assert registers <= 128 and scratch <= 32, (name, registers, scratch)
+
+
+# five wavefronts a SIMD, as many as their LDS leaves, hold 96 registers each,
+# three hold 168
+def test_moments_and_scales_of_the_deviations_leave_their_wavefronts(kernels):
+    for name, (registers, _) in _matching(kernels, "k_moments_ne", "SysNeoHooke", "D2Q9", "[df]Lb1E").items():
+        assert registers <= 96, (name, registers)
+    for name, (registers, _) in _matching(kernels, "k_init_ne", "SysNeoHooke", "D2Q9", "Lb1ELb1E").items():
+        assert registers <= 168, (name, registers)
